@@ -159,7 +159,7 @@ struct CompactArgs {
   int32_t* rank;                           // workspace [B][n_pg]: rank of each destination page
   int32_t B, K, page_size, row_bytes, n_lk;
   int32_t n_pg;                            // pages of the budget: ceil(K / page_size)
-  int32_t units;                           // 1 KiB column groups per row (set by launch_compact)
+  int32_t units;                           // KiB per row, rows of whole KiB (set by launch_compact)
 };
 
 struct InplaceArgs {
