@@ -86,6 +86,7 @@ struct ScoreLagArgs {
   float* partial;                          // [B][n_planes][segments][C]
   int32_t splits;                          // workgroups sharing one plane's rows
   float* prange;                           // [splits][2][B][L][2][H][d] partial ranges
+  int32_t first_split;                     // first chunks' ranges are in prange (set by the launcher)
 };
 
 struct LagReduceArgs {
@@ -307,6 +308,13 @@ constexpr int64_t kCompactGridX = 1 << 24;  // gather workgroups per grid row
 constexpr int kCompactWaves = kCompactThreads / 64;  // walks per in-place move workgroup
 constexpr int kLagWgWanted = 512;        // split a plane's rows until this many workgroups
 constexpr int kLagPtCache = 1024;        // page-table entries a KV-scorer workgroup keeps in LDS
+// Bytes of a call's rows from which on its first chunks' ranges are found by
+// a launch of their own (split rows only).  It cannot be known here whether
+// a stream is fresh, so later chunks of that size pay for an empty launch:
+// at 64 MiB (1 sequence, 64 planes, 512 rows of 2 KiB) 1-2 us of 25, at 128
+// MiB under 1 us of 37, while the first chunk goes from 88 to 40 us (163 ->
+// 62 us at 128 MiB, 606 -> 190 us at 512 MiB).
+constexpr int64_t kLagFirstBytes = 64 << 20;
 constexpr int kLagRowCache = kLagPtCache / 2;  // or row offsets (int64, the same LDS)
 
 // KV-vector scorer shapes (lag: a lag-normalised signal).  Wavefronts per

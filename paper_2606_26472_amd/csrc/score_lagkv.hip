@@ -46,7 +46,9 @@
 //   ranges meet in LDS, one slot each, and are reduced channel by channel
 //   in slot order.
 //   First chunk of a stream (lag-normalised): a first pass over the rows
-//   finds the chunk's range, the second computes the variances with it.
+//   finds the chunk's range, the second computes the variances with it; in
+//   one workgroup per plane, or, when the rows are many and split between
+//   workgroups, in two launches of all shares (k_lag_first_range first).
 // Per (row, plane, segment) the sum of its heads' variances goes to
 // partial[b][plane][segment][c].
 // Kernel 2 sums the planes in a fixed order and divides by L*H, and (split
@@ -191,13 +193,17 @@ __attribute__((amdgpu_waves_per_eu(LAG ? 4 : 8))) void k_score_lagkv(ScoreLagArg
   // this lane's first channel in the [2][B][L][2][H][d] range layout
   const int64_t rbase = (((int64_t)b * a.L + layer) * 2 + kv) * HD + col * NCH;
   const bool fresh = LAG && a.n_tok_in[b] <= 0;
+  // a first chunk whose range k_lag_first_range has left in `prange`: its
+  // rows are shared like any other chunk's
+  const bool ranged = LAG && fresh && a.first_split;
   // The previous chunk's range of this lane's channels (carried state),
   // loaded first as whole vectors, so that its latency overlaps the set-up
   // of the row table instead of delaying the first rows.
   float rin[LAG ? 2 * NCH : 1];
-  if (LAG && !fresh) {
-    const float4* qmn = reinterpret_cast<const float4*>(a.range_in + rbase);
-    const float4* qmx = reinterpret_cast<const float4*>(a.range_in + half + rbase);
+  if (LAG && (!fresh || ranged)) {
+    const float* r0 = ranged ? a.prange : a.range_in;
+    const float4* qmn = reinterpret_cast<const float4*>(r0 + rbase);
+    const float4* qmx = reinterpret_cast<const float4*>(r0 + half + rbase);
 #pragma unroll
     for (int k = 0; k < NCH / 4; ++k) {
       const float4 u = qmn[k], v = qmx[k];
@@ -210,15 +216,24 @@ __attribute__((amdgpu_waves_per_eu(LAG ? 4 : 8))) void k_score_lagkv(ScoreLagArg
       rin[NCH + 4 * k + 2] = v.z;
       rin[NCH + 4 * k + 3] = v.w;
     }
+    if (ranged)
+      for (int q = 1; q < a.splits; ++q) {
+        const float* rq = a.prange + (int64_t)q * 2 * half + rbase;
+#pragma unroll
+        for (int e = 0; e < NCH; ++e) {
+          rin[e] = nan_min(rin[e], rq[e]);
+          rin[NCH + e] = nan_max(rin[NCH + e], rq[half + e]);
+        }
+      }
   }
   // this segment's row of partial sums [B][plane][segment][C]
   float* part = a.partial + (((int64_t)b * a.n_planes + p) * segs + seg) * a.C;
 
   // Rows [r_lo, r_hi) of the chunk are this workgroup's.  The first chunk
-  // of a stream needs every row for its range before any variance: the
-  // first share takes it whole.
+  // of a stream needs every row for its range before any variance: unless
+  // that range is there already, the first share takes it whole.
   int r_lo = 0, r_hi = 0;
-  if (fresh) {
+  if (fresh && !ranged) {
     r_hi = sp == 0 ? a.C : 0;
   } else {
     const int per = (a.C + a.splits - 1) / a.splits;
@@ -368,29 +383,32 @@ __attribute__((amdgpu_waves_per_eu(LAG ? 4 : 8))) void k_score_lagkv(ScoreLagArg
   // (sc up to 1/eps) makes large.
   float mnv[LAG ? NCH : 1], sc[LAG ? NCH : 1];
   if (LAG) {
-    if (fresh) {
+    if (fresh && !ranged) {
       // first pass: the chunk's own range
-      for (int it = 0; it < sweeps; ++it) {
-        if (it % 64 == 0) fill_table(it);
-        uint32_t w[NW];
-        bool ok;
-        load_row(row_of(it), w, ok);
-        if (ok)
+      for (int it0 = 0; it0 < sweeps; it0 += AH) {
+        if (it0 % 64 == 0) fill_table(it0);
+        uint32_t w[AH][NW];
+        bool ok[AH];
 #pragma unroll
-          for (int k = 0; k < NW; ++k) {
-            cmn[2 * k] = nan_min(cmn[2 * k], bf16_lo(w[k]));
-            cmx[2 * k] = nan_max(cmx[2 * k], bf16_lo(w[k]));
-            cmn[2 * k + 1] = nan_min(cmn[2 * k + 1], bf16_hi(w[k]));
-            cmx[2 * k + 1] = nan_max(cmx[2 * k + 1], bf16_hi(w[k]));
-          }
+        for (int u = 0; u < AH; ++u) load_row(row_of(it0 + u), w[u], ok[u]);
+#pragma unroll
+        for (int u = 0; u < AH; ++u)
+          if (ok[u])
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+              cmn[2 * k] = nan_min(cmn[2 * k], bf16_lo(w[u][k]));
+              cmx[2 * k] = nan_max(cmx[2 * k], bf16_lo(w[u][k]));
+              cmn[2 * k + 1] = nan_min(cmn[2 * k + 1], bf16_hi(w[u][k]));
+              cmx[2 * k + 1] = nan_max(cmx[2 * k + 1], bf16_hi(w[u][k]));
+            }
       }
       deposit();
       combine(true);
     }
 #pragma unroll
     for (int e = 0; e < NCH; ++e) {
-      const float mn = fresh ? lds[col * NCH + e] : rin[e];
-      const float mx = fresh ? lds[HD + col * NCH + e] : rin[NCH + e];
+      const float mn = fresh && !ranged ? lds[col * NCH + e] : rin[e];
+      const float mx = fresh && !ranged ? lds[HD + col * NCH + e] : rin[NCH + e];
       mnv[e] = mn;
       sc[e] = __builtin_amdgcn_rcpf(mx - mn + a.eps);  // (one reciprocal instruction)
     }
@@ -578,6 +596,106 @@ __attribute__((amdgpu_waves_per_eu(LAG ? 4 : 8))) void k_score_lagkv(ScoreLagArg
     deposit();
     combine(false);
   }
+  // (a first chunk ranged beforehand: prange is complete already)
+}
+
+// The range of a first chunk (lag-normalised signals, rows split between
+// workgroups, at least kLagFirstBytes of them): share z of plane x leaves the minimum and
+// maximum of its rows in prange[z], as the score kernel does for later
+// chunks.  A sequence that is not fresh has nothing to do here.
+// Thread t owns the 8 channels of column t % (H*d / 8); the workgroup's row
+// slots take consecutive rows, kFirstAhead sweeps in flight, offsets from
+// an LDS table of kFirstTab rows.  The rows are walked from the share's end
+// to its start: the score kernel then reads them front to back and finds
+// what was read last still in the memory-side cache.  Bound by the two
+// reads of the rows: 4096 rows of 2 KiB in 64 planes (537 MB) 606 us with
+// one workgroup per plane, 190 us so (5.7 TB/s over both reads).
+constexpr int kFirstThreads = 512;
+constexpr int kFirstAhead = 8;
+constexpr int kFirstTab = 512;
+
+__global__ __launch_bounds__(kFirstThreads) void k_lag_first_range(ScoreLagArgs a) {
+  __shared__ int64_t tab[kFirstTab];
+  __shared__ __align__(16) float red[kFirstThreads * 16];
+  const int b = blockIdx.y;
+  if (a.n_tok_in[b] > 0) return;
+  const int tid = threadIdx.x;
+  const int p = blockIdx.x;
+  const int sp = blockIdx.z;
+  const int layer = a.two ? p >> 1 : p;
+  const int kv = a.two ? (p & 1) : a.kv0;
+  const int HD = a.H * a.d;
+  const int cols = HD / 8;                  // divides kScoreThreads, hence kFirstThreads
+  const int slots = kFirstThreads / cols;   // rows per sweep
+  const int slot = tid / cols;
+  const int col = tid - slot * cols;
+  const int row_bytes = HD * 2;
+  const int N = a.n_cached[b];
+  const int start = N - a.C;
+  const bool seq_ok = start >= 0 && (int64_t)((N - 1) / a.page_size) < a.ld_pt;
+  const int32_t* pt = a.pt + (int64_t)b * a.ld_pt;
+  const char* pbase = a.base + (int64_t)layer * a.s_layer + (int64_t)kv * a.s_kv + col * 16;
+  const int per = (a.C + a.splits - 1) / a.splits;
+  const int r_lo = min(a.C, sp * per);
+  const int r_hi = seq_ok ? min(a.C, r_lo + per) : r_lo;
+  float mn[8], mx[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    mn[e] = __builtin_huge_valf();
+    mx[e] = -__builtin_huge_valf();
+  }
+  for (int t1 = r_hi; t1 > r_lo; t1 -= kFirstTab) {
+    const int t0 = max(r_lo, t1 - kFirstTab);
+    __syncthreads();  // (the previous table's readers are done)
+    for (int i = tid; i < t1 - t0; i += kFirstThreads) {
+      const int pos = start + t0 + i;
+      const int pidx = a.page_shift >= 0 ? pos >> a.page_shift : pos / a.page_size;
+      const int pg = pt[pidx];
+      tab[i] = (pg < 0 || pg >= a.n_pages)
+                   ? -1
+                   : (int64_t)pg * a.s_page + (int64_t)(pos - pidx * a.page_size) * row_bytes;
+    }
+    __syncthreads();
+    for (int q = t1 - t0; q > 0; q -= kFirstAhead * slots) {
+      u32x4 w[kFirstAhead];
+      bool ok[kFirstAhead];
+#pragma unroll
+      for (int u = 0; u < kFirstAhead; ++u) {
+        const int i = q - 1 - (u * slots + slot);
+        const int64_t off = i >= 0 ? ((const lds_i64*)tab)[i] : -1;
+        ok[u] = off >= 0;
+        // (every load is issued; a missing row reads the plane's first)
+        w[u] = *reinterpret_cast<const u32x4*>(pbase + (ok[u] ? off : 0));
+      }
+#pragma unroll
+      for (int u = 0; u < kFirstAhead; ++u)
+        if (ok[u])
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            mn[2 * k] = nan_min(mn[2 * k], bf16_lo(w[u][k]));
+            mx[2 * k] = nan_max(mx[2 * k], bf16_lo(w[u][k]));
+            mn[2 * k + 1] = nan_min(mn[2 * k + 1], bf16_hi(w[u][k]));
+            mx[2 * k + 1] = nan_max(mx[2 * k + 1], bf16_hi(w[u][k]));
+          }
+    }
+  }
+  // the row slots' ranges, [slot][2][HD], reduced in slot order
+  float* mine = red + slot * 2 * HD + col * 8;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    mine[e] = mn[e];
+    mine[HD + e] = mx[e];
+  }
+  __syncthreads();
+  const int64_t half = (int64_t)a.B * a.L * 2 * HD;
+  float* dst = a.prange + (int64_t)sp * 2 * half + (((int64_t)b * a.L + layer) * 2 + kv) * HD;
+  for (int i = tid; i < 2 * HD; i += kFirstThreads) {
+    const bool lo = i < HD;
+    float v = red[i];
+    for (int k = 1; k < slots; ++k)
+      v = lo ? nan_min(v, red[k * 2 * HD + i]) : nan_max(v, red[k * 2 * HD + i]);
+    dst[lo ? i : half + i - HD] = v;
+  }
 }
 
 // Blocks [0, tok_blocks) of each sequence: q(t) = the sum of token t's
@@ -601,7 +719,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_lag_reduce(LagReduceArgs a) {
     float s = 0.f;
     if (c < a.C) {
       const float* p = a.partial + (int64_t)b * a.n_sums * a.C + c;
-#pragma unroll 8
+#pragma unroll 16
       for (int pl = part; pl < a.n_sums; pl += kRedParts) s += p[(int64_t)pl * a.C];
     }
     red[part][t] = s;
@@ -623,6 +741,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_lag_reduce(LagReduceArgs a) {
   if (kv == 0 ? a.use_k : a.use_v) {
     lo = a.prange[o];
     hi = a.prange[half + o];
+#pragma unroll 4
     for (int sp = 1; sp < a.splits; ++sp) {
       lo = nan_min(lo, a.prange[sp * 2 * half + o]);
       hi = nan_max(hi, a.prange[sp * 2 * half + half + o]);
@@ -651,10 +770,21 @@ size_t lagkv_lds_bytes(int H, int d, bool lag, bool big) {
          kLagPtCache * sizeof(int);
 }
 
-hipError_t launch_score_lagkv(const ScoreLagArgs& a, const LagReduceArgs& r, hipStream_t s) {
+hipError_t launch_score_lagkv(const ScoreLagArgs& args, const LagReduceArgs& r, hipStream_t s) {
+  ScoreLagArgs a = args;
+  a.first_split = a.lag && a.splits > 1 &&
+                  (int64_t)a.n_planes * a.B * a.C * (a.H * a.d * 2) >= kLagFirstBytes;
+  if (a.first_split) {
+    hipLaunchKernelGGL(k_lag_first_range, dim3(a.n_planes, a.B, a.splits), dim3(kFirstThreads), 0, s,
+                       a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   const bool wide = lagkv_wide(a.H, a.d, a.lag);
-  // (a stream's first chunk is one share of all C rows, so C bounds a share)
-  const bool rt = a.C <= kLagRowCache;
+  // (a stream's first chunk is one share of all C rows unless its range
+  // was found beforehand)
+  const bool whole = a.lag && !a.first_split;
+  const bool rt = (whole ? a.C : (a.C + a.splits - 1) / a.splits) <= kLagRowCache;
   const bool big = lagkv_big(a.H, a.d, a.lag, (int64_t)a.n_planes * a.B);
   const hipError_t e =
       a.lag ? (!wide ? launch_lag<true, false, kLagWords>(a, s)
