@@ -270,6 +270,8 @@ __device__ __forceinline__ float band_combine(const float (*vals)[TILE], int t, 
 // ---------------------------------------------------------------------------
 // Launchers (return the HIP error of the launch; never synchronise)
 // ---------------------------------------------------------------------------
+// Compute units of the current device (0 if the query fails).
+int device_cus();
 hipError_t launch_score_hs(const ScoreHsArgs& a, hipStream_t s);
 hipError_t launch_score_tokens(const ScoreTokArgs& a, hipStream_t s);
 hipError_t launch_score_lagkv(const ScoreLagArgs& a, const LagReduceArgs& r,

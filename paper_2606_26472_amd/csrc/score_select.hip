@@ -6,35 +6,50 @@
 // side by side instead of one after the other.
 //
 // Workgroups [0, B) are the select kernel's (one sequence each); the rest
-// carry 16 score wavefronts each (each wavefront one (sequence, layer,
+// carry up to 16 score wavefronts each (each wavefront one (sequence, layer,
 // segment) unit, barrier-free).  Both run the very code of their own
 // kernels (select_impl.h, score_hs_impl.h), so the results are those of the
 // separate launches bit for bit.
+#include <algorithm>
+
 #include "score_hs_impl.h"
 #include "select_impl.h"
 
 namespace epikv {
 namespace {
 
-constexpr int kUnitsPerBlock = kSelectThreads / 64;
+constexpr int kMaxUnits = kSelectThreads / 64;  // score units per workgroup, at most
 
 template <int KPT, int VPW, int U>
-__global__ __launch_bounds__(kSelectThreads) void k_select_score(SelectArgs sel, ScoreHsArgs sc) {
+__global__ __launch_bounds__(kSelectThreads) void k_select_score(SelectArgs sel, ScoreHsArgs sc,
+                                                                 int units) {
   if ((int)blockIdx.x < sel.B) {
     select_impl::select_seq<KPT>(sel, blockIdx.x);
     return;
   }
-  const int64_t unit = (int64_t)(blockIdx.x - sel.B) * kUnitsPerBlock + (threadIdx.x >> 6);
+  const int wave = threadIdx.x >> 6;
+  if (wave >= units) return;
+  const int64_t unit = (int64_t)(blockIdx.x - sel.B) * units + wave;
   if (unit >= score_impl::wave_units(sc)) return;
   score_impl::score_hs_unit<VPW, U>(sc, (int)unit, threadIdx.x & 63);
 }
 
 template <int KPT, int VPW, int U>
 hipError_t launch(const SelectArgs& sel, const ScoreHsArgs& sc, hipStream_t s) {
-  const int64_t units = score_impl::wave_units(sc);
-  const int64_t blocks = sel.B + (units + kUnitsPerBlock - 1) / kUnitsPerBlock;
+  const int64_t total = score_impl::wave_units(sc);
+  // As few units per workgroup as put all of them on the compute units that
+  // the selection leaves free: with 16 each, a batch of 32 x 128 tokens had
+  // its 1,920 units on 120 of 256 compute units.  16 -> as few (launch of
+  // the selection of ragged 8k-32k caches and 15 layers of 4096): 12
+  // sequences 53.7 -> 38.0 us, 32 sequences 112.7 -> 87.6 us; 16 sequences
+  // at 4224 cached 62.4 -> 48.2 us, 1 sequence 16.5 -> 12.6 us (now the
+  // selection's time).  Two rows in flight per wavefront spill 11 registers
+  // (47 and 103 us for the first two).
+  const int64_t free_cus = std::max(1, device_cus() - sel.B);
+  const int64_t units = std::min<int64_t>(kMaxUnits, (total + free_cus - 1) / free_cus);
+  const int64_t blocks = sel.B + (total + units - 1) / units;
   hipLaunchKernelGGL((k_select_score<KPT, VPW, U>), dim3((unsigned)blocks), dim3(kSelectThreads), 0,
-                     s, sel, sc);
+                     s, sel, sc, (int)units);
   return hipGetLastError();
 }
 

@@ -491,23 +491,6 @@ hipError_t launch(const SelectMultiArgs& m, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Compute units of the current device (0 if the query fails), looked up
-// once per device.  The grid is kept within one workgroup per unit: that is
-// always resident, and measured faster than sharing units between two.
-int device_cus() {
-  constexpr int kMaxDevices = 64;
-  static std::atomic<int> cache[kMaxDevices];
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-  int v = cache[dev].load(std::memory_order_relaxed);
-  if (v <= 0) {
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      return 0;
-    cache[dev].store(v, std::memory_order_relaxed);
-  }
-  return v;
-}
-
 constexpr size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 // Every sequence's scratch block made clear before the selection: head
@@ -522,6 +505,21 @@ __global__ __launch_bounds__(256) void k_select_scratch_clear(uint32_t* scratch,
 
 }  // namespace
 
+// Looked up once per device.
+int device_cus() {
+  constexpr int kMaxDevices = 64;
+  static std::atomic<int> cache[kMaxDevices];
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+  int v = cache[dev].load(std::memory_order_relaxed);
+  if (v <= 0) {
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      return 0;
+    cache[dev].store(v, std::memory_order_relaxed);
+  }
+  return v;
+}
+
 size_t select_scratch_bytes(int B) {
   if (B < 1 || 2 * B > kSelMaxGrid) return 0;  // never split: at most one workgroup each
   return align256((size_t)B * kSelSeqWords * 4 + (size_t)kSelMaxGrid * 8);
@@ -530,7 +528,8 @@ size_t select_scratch_bytes(int B) {
 hipError_t launch_select_groups(const SelectArgs& a, void* scratch, hipStream_t s) {
   // The fewest keys per thread (1, 2, 4, 8 or 16; 32 would spill) whose
   // grid fits one workgroup per compute unit, so that a sequence's
-  // workgroups all run together.
+  // workgroups all run together (always resident, and measured faster than
+  // sharing units between two).
   int v = -1, groups = 1;
   const int64_t cap = min(kSelMaxGrid, device_cus());
   if (scratch && select_scratch_bytes(a.B) > 0) {
