@@ -840,7 +840,8 @@ def copy_ceiling(n_bytes: int = 4 << 30, reps: int = 5):
     return shapes[best][0], shapes[best][1], best, gbps
 
 
-COMPACT_SOURCES = ("paper_2606_26472_amd/csrc/compact.hip",)
+COMPACT_SOURCES = ("paper_2606_26472_amd/csrc/compact.hip",
+                   "paper_2606_26472_amd/csrc/compact_impl.h")
 
 
 def compact_source_hash() -> str:

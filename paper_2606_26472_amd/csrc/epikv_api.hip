@@ -868,6 +868,11 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
                                      io->keep_idx, io->n_keep, io->seq_status, io->chunk);
   const ZscoreArgs zs = zscore_args(cfg, io->chunk, sig, io->n_cached, io->state_in, io->state_out,
                                     io->scores, io->ld_s, nullptr);
+  CompactArgs ca;
+  if (!io->in_place)
+    ca = compact_args(cfg, &io->src, io->src_pt, io->ld_src_pt, &io->dst, io->dst_pt,
+                      io->ld_dst_pt, io->keep_idx, io->n_keep, src_scores, io->dst_scores,
+                      io->src_pos, io->dst_pos, io->ld_s, io->seq_status, ws_offsets);
   bool selected = false;  // the select stage is on the stream
   if (!scoring) {
     st = launched(launch_select_groups(sel, ws_select, stream));
@@ -878,10 +883,15 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
         hs_args(cfg, io->chunk, io->hidden, io->ld_tok, io->ld_seq, io->state_in, io->state_out, sig);
     if (select_score_fusable(sel, hs)) {
       // The chunk lies inside the recency window: selection needs only the
-      // older, frozen scores, so it runs beside the scoring, then the
-      // chunk's scores are smoothed and written.
-      st = launched(launch_select_score(sel, hs, stream));
+      // older, frozen scores, so it runs beside the scoring (and the
+      // ordering of the destination pages), then the chunk's scores are
+      // smoothed and written (beside the resolve stage).
+      st = launched(launch_select_score(sel, hs, io->in_place ? nullptr : &ca, stream));
       if (st) return st;
+      if (!io->in_place) {
+        st = launched(launch_smooth_resolve(zs, ca, stream));
+        return st ? st : launched(launch_compact_gather(ca, stream));
+      }
       st = launched(launch_zscore(zs, stream));
       if (st) return st;
       selected = true;
@@ -903,9 +913,5 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
     if (io->in_place == EPIKV_COMPACT_REMAP) a = remap_args(a, const_cast<int32_t*>(io->src_pt));
     return launched(launch_compact_inplace(a, stream));
   }
-  return launched(launch_compact(
-      compact_args(cfg, &io->src, io->src_pt, io->ld_src_pt, &io->dst, io->dst_pt, io->ld_dst_pt,
-                   io->keep_idx, io->n_keep, src_scores, io->dst_scores,
-                   io->src_pos, io->dst_pos, io->ld_s, io->seq_status, ws_offsets),
-      stream));
+  return launched(launch_compact(ca, stream));
 }

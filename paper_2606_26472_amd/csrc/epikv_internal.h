@@ -286,8 +286,16 @@ size_t select_scratch_bytes(int B);
 // Selection and hidden-state scoring in one launch; valid only when
 // select_score_fusable (the chunk lies inside the recency window).
 bool select_score_fusable(const SelectArgs& sel, const ScoreHsArgs& sc);
-hipError_t launch_select_score(const SelectArgs& sel, const ScoreHsArgs& sc, hipStream_t s);
-hipError_t launch_compact(const CompactArgs& a, hipStream_t s);
+// With `ca`, also the order stage of that rebuild.
+hipError_t launch_select_score(const SelectArgs& sel, const ScoreHsArgs& sc, const CompactArgs* ca,
+                               hipStream_t s);
+// Smoothing and, for a step whose selection is on the stream and whose chunk
+// it keeps whole, the resolve stage of an out-of-place rebuild.
+hipError_t launch_smooth_resolve(const ZscoreArgs& a, const CompactArgs& ca, hipStream_t s);
+hipError_t launch_compact(const CompactArgs& a, hipStream_t s);  // its three stages
+hipError_t launch_compact_order(const CompactArgs& a, hipStream_t s);
+hipError_t launch_compact_resolve(const CompactArgs& a, hipStream_t s);
+hipError_t launch_compact_gather(const CompactArgs& a, hipStream_t s);
 hipError_t launch_compact_inplace(const InplaceArgs& a, hipStream_t s);
 hipError_t launch_fill(const FillArgs& a, hipStream_t s);
 

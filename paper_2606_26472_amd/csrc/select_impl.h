@@ -135,6 +135,16 @@ __device__ __forceinline__ void find_digit(const uint32_t* hist, int nb, uint32_
   }
 }
 
+// Rows kept of sequence b, or negative if it is refused: all that the counts
+// say before any score is looked at.
+__device__ __forceinline__ int expected_keep(const SelectArgs& a, int b) {
+  const int N = a.n_cached[b];
+  const int P = a.n_prefix[b];
+  if (N < a.min_n || (int64_t)N > a.ld_s || P < 0) return -1;
+  if (N <= a.K) return N;
+  return (int64_t)P + a.R >= a.K ? -1 : a.K;
+}
+
 // KPT > 0: positions [tid*KPT, (tid+1)*KPT) have their keys in registers.
 // KPT == 0: keys are recomputed from global memory in every sweep.
 template <int KPT>

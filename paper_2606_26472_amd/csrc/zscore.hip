@@ -1,256 +1,34 @@
-// Causal trailing-window smoothing and band combination.
-//   Eq. 3:  z(t) = (x(t) - mu(t)) / (sigma(t) + eps)     (EPIKV_SMOOTH_Z)
-//   Eq. 2:  mu(t)                                          (EPIKV_SMOOTH_MEAN)
-// with mu and the population sigma over the last min(w, available) samples
-// up to and including t; then s(t) = mean_A - mean_B over the signal rows
-// (Fig. 1; the Lag-KV signal is a single row of weight +1).  s(t) is the
-// token's frozen score (Sec. 3.3).
-//
-// One 1024-thread workgroup scores a tile of kZscoreTile (64) tokens of one
-// sequence; each of its 16 wavefronts smooths one signal row at a time (lane
-// = token), so the band layers are processed in parallel.  A wavefront
-// stages its row's tile plus the w-1 samples before it in its own LDS slice
-// (taken from the carried ring for the chunk's first tokens) and each lane
-// computes its window's mean and variance in two passes over at most w
-// values (fp32; the two-pass form avoids the E[x^2] - mu^2 cancellation when
-// the signal's mean is large against its spread).  The per-row values meet
-// in LDS for the band combination.
-#include "epikv_internal.h"
+// The smoothing kernels (zscore_impl.h, which describes the method): one
+// workgroup per 64-token tile of a sequence, or per few tiles (EMA).
+#include "zscore_impl.h"
 
 namespace epikv {
 namespace {
 
-constexpr int kWaves = kZscoreThreads / 64;
-constexpr int kZscoreWaves = kWaves;
-constexpr int kSlice = EPIKV_MAX_WINDOW - 1 + kZscoreTile;
-constexpr int kEmaWg = 256;
-
 __global__ __launch_bounds__(kZscoreThreads) void k_zscore(ZscoreArgs a) {
-  __shared__ float xs[kWaves][kSlice];
-  __shared__ float vals[EPIKV_MAX_BAND][kZscoreTile];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int tile = blockIdx.x;
-  const int b = blockIdx.y;
-  const int wm1 = a.w - 1;
-  const int c = tile * kZscoreTile + lane;
-  // (both counts are read here, so that neither waits on its own)
-  const int N = a.n_cached[b];
-  const int n_tok = max(a.n_tok_in[b], 0);
-  // The first token of a fresh hidden-state stream has no predecessor and
-  // hence no sample.
-  const int c0 = (a.hs && n_tok == 0) ? 1 : 0;
-  const int64_t prior = a.hs ? (int64_t)max(n_tok - 1, 0) : (int64_t)n_tok;
-  const int cnt = (int)min((int64_t)wm1, prior);
-  // Extended index space: X[j] = ring slot j for j < w-1, X[w-1+c] = signal
-  // of token c.  Valid samples are X[vstart ..].
-  const int vstart = wm1 - cnt + c0;
-  const bool last_tile = (tile == (int)gridDim.x - 1);
-  const int base = tile * kZscoreTile;  // X index held in xs[wave][0]
-  const int span = wm1 + kZscoreTile;
-  const int64_t total_out = prior + (a.C - c0);
-  const int cnt_out = (int)min((int64_t)wm1, total_out);
-  float* x = xs[wave];
-
-  // Every wavefront runs the same number of rounds so the barriers match.
-  const int rounds = (a.n_sig + kWaves - 1) / kWaves;
-  for (int rd = 0; rd < rounds; ++rd) {
-    const int l = rd * kWaves + wave;
-    const bool active = l < a.n_sig;
-    if (active) {
-      const float* ring = a.ring_in + ((int64_t)b * a.n_sig + l) * wm1;
-      const float* sg = a.sig + ((int64_t)l * a.B + b) * a.C;
-      for (int k = lane; k < span; k += 64) {
-        const int j = base + k;
-        float v = 0.f;
-        if (j < wm1)
-          v = ring[j];
-        else if (j - wm1 < a.C)
-          v = sg[j - wm1];
-        x[k] = v;
-      }
-    }
-    __syncthreads();
-    if (active) {
-      float v = 0.f;
-      if (c < a.C && c >= c0) {
-        const int j = wm1 + c;
-        v = smooth_at(x, base, max(vstart, j - wm1), j, a.mode, a.eps);
-      }
-      vals[l][lane] = v;
-      if (a.smoothed && c < a.C) a.smoothed[((int64_t)l * a.B + b) * a.C + c] = v;
-      if (last_tile) {
-        // Carry the last min(w-1, samples) samples, right-aligned: slot k
-        // holds X[C + k].
-        float* ro = a.ring_out + ((int64_t)b * a.n_sig + l) * wm1;
-        for (int k = lane; k < wm1; k += 64) {
-          const bool valid = (wm1 - 1 - k) < cnt_out;
-          ro[k] = valid ? x[a.C + k - base] : 0.f;
-        }
-      }
-    }
-    __syncthreads();
-  }
-
-  if (tid < kZscoreTile && c < a.C) {
-    const float s = band_combine<kZscoreTile>(vals, tid, a.n_a, a.n_sig, a.n_b);
-    if (N >= a.C && (int64_t)N <= a.ld_s) a.scores[(int64_t)b * a.ld_s + (N - a.C) + c] = s;
-  }
-  if (last_tile && tid == 0) a.n_tok_out[b] = n_tok + a.C;
-  if (last_tile && tid < a.n_sig)
-    a.ema_out[(int64_t)b * a.n_sig + tid] = a.ema_in[(int64_t)b * a.n_sig + tid];
-}
-
-// EMA smoothing (App. E): y(t) = alpha*y(t-1) + (1-alpha)*x(t), y = x at the
-// stream's first sample.  For each signal row a wavefront turns a 64-token
-// tile into per-token affine maps y -> A*y + Bc (a token without a sample is
-// the identity) and composes them with a lane-wise inclusive scan, so the
-// tile's averages follow exactly from the average carried in from the
-// previous tile.  The per-row values meet in LDS for the band combination.
-//
-// A workgroup has `per` consecutive tiles.  The average carried into the
-// first of them comes from the workgroup itself, from all the samples before
-// them: a tile's composed map at its last token does not need the carry, and
-// only that token's is needed, so it is a tree of 63 multiply-adds (the
-// scan's own at lane 63, in its order: the carry has the same bits as when
-// the tiles were scanned one after the other) over the samples four to a
-// lane, and the tiles' maps are applied to the carry in order.  Reading the
-// samples again costs a last workgroup about 0.04 us per tile before it;
-// one workgroup walking all tiles cost 1.7 us per tile, a chain of load,
-// scan and barriers (15 rows; 2 x 6001 tokens 149 -> 11.5 us, 65,536 tokens
-// 1704 -> 74 us, 64 x 1000 tokens 28 -> 11 us).
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_from(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
-// The carry after tiles [1, first) of row x, from the one after tile 0.
-__device__ __forceinline__ float ema_carry(const float* x, int first, float al, float bl,
-                                           float carry, int lane) {
-  const float a1 = al * al, a2 = a1 * a1, a3 = a2 * a2, a4 = a3 * a3, a5 = a4 * a4, a6 = a5 * a5;
-  constexpr int U = 4;  // loads in flight, four tiles each
-  for (int q = 1; q < first; q += 4 * U) {
-    f32x4u v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = q + 4 * u + (lane >> 4);  // this lane's tile
-      const int tc = t < first ? t : 0;       // (tile 0 in place of one past the range)
-      v[u] = *reinterpret_cast<const f32x4u*>(x + (int64_t)tc * kZscoreTile + 4 * (lane & 15));
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float b01 = fmaf(al, bl * v[u][0], bl * v[u][1]);
-      const float b23 = fmaf(al, bl * v[u][2], bl * v[u][3]);
-      float m = fmaf(a1, b01, b23);
-      m = fmaf(a2, dpp_from<0x111>(m), m);  // row_shr:1, 2, 4, 8: lane 15 of
-      m = fmaf(a3, dpp_from<0x112>(m), m);  // each row of 16 ends with its
-      m = fmaf(a4, dpp_from<0x114>(m), m);  // tile's composed map
-      m = fmaf(a5, dpp_from<0x118>(m), m);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float bk =
-            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 16 * k + 15));
-        if (q + 4 * u + k < first) carry = fmaf(a6, carry, bk);
-      }
-    }
-  }
-  return carry;
+  zscore_impl::zscore_tile(a, blockIdx.x, gridDim.x, blockIdx.y,
+                           [&](int b, int c, int N, float s) {
+                             zscore_impl::put_score(a, b, c, N, s);
+                           });
 }
 
 __global__ __launch_bounds__(kZscoreThreads) void k_ema(ZscoreArgs a, int per) {
-  __shared__ float carry[EPIKV_MAX_BAND];
-  __shared__ float vals[EPIKV_MAX_BAND][kZscoreTile];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int b = blockIdx.y;
-  const int wm1 = a.w - 1;
-  const int N = a.n_cached[b];
-  const int n_tok = max(a.n_tok_in[b], 0);
-  const int c0 = (a.hs && n_tok == 0) ? 1 : 0;
-  const int64_t prior = a.hs ? (int64_t)max(n_tok - 1, 0) : (int64_t)n_tok;
-  const float al = a.alpha, bl = 1.0f - a.alpha;
-  const bool write_scores = N >= a.C && (int64_t)N <= a.ld_s;
-  const int rounds = (a.n_sig + kZscoreWaves - 1) / kZscoreWaves;
-  const int tiles = (a.C + kZscoreTile - 1) / kZscoreTile;
-  const int first = blockIdx.x * per;
-  const int last = min(tiles, first + per);
-  // One row's tile: each token's average given the one carried in.
-  auto scan_tile = [&](const float* x, int tile, float cin, bool* has) -> float {
-    const int c = tile * kZscoreTile + lane;
-    *has = c < a.C && c >= c0;
-    // (the stream's first sample starts the average)
-    return ema_scan(*has ? x[c] : 0.f, *has, prior == 0 && c == c0, al, bl, cin, lane);
-  };
-  // The average carried into this workgroup's first tile; each row's stays
-  // with its wavefront, and is read by that wavefront alone.
-  for (int l = wave; l < a.n_sig; l += kZscoreWaves) {
-    const float* x = a.sig + ((int64_t)l * a.B + b) * a.C;
-    float y = a.ema_in[(int64_t)b * a.n_sig + l];
-    if (first > 0) {
-      bool has;
-      y = __shfl(scan_tile(x, 0, y, &has), 63, 64);
-      y = ema_carry(x, first, al, bl, y, lane);
-    }
-    if (lane == 0) carry[l] = y;
-  }
-  __syncthreads();
-  for (int tile = first; tile < last; ++tile) {
-    const int c = tile * kZscoreTile + lane;
-    for (int rd = 0; rd < rounds; ++rd) {
-      const int l = rd * kZscoreWaves + wave;
-      if (l < a.n_sig) {
-        bool has;
-        const float y = scan_tile(a.sig + ((int64_t)l * a.B + b) * a.C, tile, carry[l], &has);
-        const float v = has ? y : 0.f;
-        vals[l][lane] = v;
-        if (a.smoothed && c < a.C) a.smoothed[((int64_t)l * a.B + b) * a.C + c] = v;
-        const float y_last = __shfl(y, 63, 64);
-        if (lane == 0) carry[l] = y_last;
-      }
-    }
-    __syncthreads();
-    if (tid < kZscoreTile && c < a.C && write_scores)
-      a.scores[(int64_t)b * a.ld_s + (N - a.C) + c] =
-          band_combine<kZscoreTile>(vals, tid, a.n_a, a.n_sig, a.n_b);
-    __syncthreads();
-  }
-  if (last < tiles) return;
-  // carried state: averages, sample ring, token count
-  if (tid < a.n_sig) a.ema_out[(int64_t)b * a.n_sig + tid] = carry[tid];
-  const int64_t total_out = prior + (a.C - c0);
-  const int cnt_out = (int)min((int64_t)wm1, total_out);
-  for (int i = tid; i < a.n_sig * wm1; i += kZscoreThreads) {
-    const int l = i / wm1;
-    const int k = i - l * wm1;
-    const int j = a.C + k;  // index in [ring | chunk signal]
-    float v = 0.f;
-    if ((wm1 - 1 - k) < cnt_out)
-      v = j < wm1 ? a.ring_in[((int64_t)b * a.n_sig + l) * wm1 + j]
-                  : a.sig[((int64_t)l * a.B + b) * a.C + (j - wm1)];
-    a.ring_out[((int64_t)b * a.n_sig + l) * wm1 + k] = v;
-  }
-  if (tid == 0) a.n_tok_out[b] = n_tok + a.C;
+  zscore_impl::ema_tiles(a, blockIdx.x, per, blockIdx.y, [&](int b, int c, int N, float s) {
+    zscore_impl::put_score(a, b, c, N, s);
+  });
 }
 
 }  // namespace
 
 hipError_t launch_zscore(const ZscoreArgs& a, hipStream_t s) {
+  const int tiles = zscore_impl::tiles_of(a);
   if (a.mode == EPIKV_SMOOTH_EMA) {
-    // One tile per workgroup until there are kEmaWg of them, about one per
-    // compute unit; from there on more tiles each, since a further
-    // workgroup reads all the samples before it again.
-    const int64_t tiles = (a.C + kZscoreTile - 1) / kZscoreTile;
-    const int64_t per = (tiles * a.B + kEmaWg - 1) / kEmaWg;
-    hipLaunchKernelGGL(k_ema, dim3((unsigned)((tiles + per - 1) / per), a.B), dim3(kZscoreThreads), 0,
-                       s, a, (int)per);
+    const int per = zscore_impl::ema_per(a);
+    hipLaunchKernelGGL(k_ema, dim3((tiles + per - 1) / per, a.B), dim3(kZscoreThreads), 0, s, a,
+                       per);
     return hipGetLastError();
   }
-  dim3 grid((a.C + kZscoreTile - 1) / kZscoreTile, a.B);
-  hipLaunchKernelGGL(k_zscore, grid, dim3(kZscoreThreads), 0, s, a);
+  hipLaunchKernelGGL(k_zscore, dim3(tiles, a.B), dim3(kZscoreThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -1,0 +1,122 @@
+"""The eviction step's merged launches (select + score + page order, then
+smoothing + resolve) against its stages called one by one, bit for bit."""
+import numpy as np
+import pytest
+
+import synth
+from harness import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2606_26472_amd import epikv
+    epikv.lib()
+    return epikv
+
+
+# lengths: longer than K, at K, shorter, exactly the chunk, too short for it
+RAGGED = [700, 256, 200, None, 1]
+
+
+@pytest.mark.parametrize("smoothing", ["z", "mean", "raw", "ema"])
+@pytest.mark.parametrize("C,page,order,bad", [
+    (64, 16, "scattered", False), (1, 3, "scattered", True), (33, 16, "rising", True),
+    (64, 1, "scattered", False)])
+def test_step_equals_its_stages(E, smoothing, C, page, order, bad):
+    """Sequences of every kind (longer than the budget, at it, shorter, as
+    long as the chunk, shorter than it: refused), one whose prefix leaves no
+    room (refused), and, with `bad`, tables that hold ids out of range for a
+    page in the middle and for the page of the chunk's tail."""
+    _compare(E, smoothing, C, page, order, bad, RAGGED, 256)
+
+
+@pytest.mark.parametrize("smoothing", ["z", "ema"])
+def test_many_sequences(E, smoothing):
+    """Two smoothing tiles for each of 140 sequences (EMA: both with one
+    workgroup), several score units per workgroup, budgets of 512."""
+    _compare(E, smoothing, 100, 16, "scattered", False, [600, 512, 130, 513] * 35, 512)
+
+
+def _compare(E, smoothing, C, page, order, bad, lengths, K):
+    import torch
+    print(f"merged step {smoothing} C={C} page={page} {order} bad={bad}", flush=True)
+    g = synth.rng(2100 + C + page)
+    lengths = np.array([C if n is None else n for n in lengths] + [K + 50])
+    B, L, H, d, D, na, nb = lengths.size, 1, 1, 64, 64, 3, 2
+    ld_s = int(lengths.max())
+    cfg = E.default_cfg(batch=B, hidden=D, n_layers=L, n_kv_heads=H, head_dim=d, page_size=page,
+                        n_band_a=na, n_band_b=nb, budget=K,
+                        smoothing=getattr(E, "SMOOTH_" + smoothing.upper()))
+    assert C <= min(128, K // 4)
+    src_pt, n_src = synth.page_tables(lengths, page, g)
+    if order == "rising":
+        dst_pt, n_dst = synth.contiguous_page_tables(np.full(B, K), page, first=1)
+    else:
+        dst_pt, n_dst = synth.page_tables(np.full(B, K), page, g)
+    if bad:
+        src_pt[0, (lengths[0] - 1) // page] = n_src          # the chunk's last page
+        dst_pt[1, 3] = -1
+        dst_pt[2, (lengths[2] - 1) // page] = n_dst + 5      # the last kept row's page
+    pool = dev(synth.random_bits16(g, (L, 2, n_src, page, H * d)))
+    hid = dev(synth.f32_to_bf16_bits(g.standard_normal((na + nb, B, C, D)).astype(np.float32)))
+    sc = g.standard_normal((B, ld_s)).astype(np.float32)
+    st_in = torch.zeros(E.state_bytes(cfg), dtype=torch.uint8, device="cuda")
+    sec = E.state_sections(cfg, st_in)
+    n_tok = np.maximum(lengths - C, 0).astype(np.int32)
+    sec["n_tok"].copy_(dev(n_tok))
+    sec["ring"].copy_(dev((20 + g.standard_normal(tuple(sec["ring"].shape))).astype(np.float32)))
+    sec["ema"].copy_(dev((20 + g.standard_normal(tuple(sec["ema"].shape))).astype(np.float32)))
+    n_cached = dev(lengths.astype(np.int32))
+    prefix = np.zeros(B, np.int32)
+    prefix[-1] = K
+    n_prefix = dev(prefix)
+    pos = dev(np.tile(np.arange(ld_s, dtype=np.int32), (B, 1)))
+    hidden = [hid[l] for l in range(na + nb)]
+
+    def outputs():
+        return dict(dst=torch.full((L, 2, n_dst, page, H * d), 77, dtype=torch.int16,
+                                   device="cuda"),
+                    scores=dev(sc), dsc=torch.full((B, ld_s), -9.0, device="cuda"),
+                    dpos=torch.full((B, ld_s), -9, dtype=torch.int32, device="cuda"),
+                    keep=torch.full((B, K), -5, dtype=torch.int32, device="cuda"),
+                    nk=torch.zeros(B, dtype=torch.int32, device="cuda"),
+                    status=torch.zeros(B, dtype=torch.int32, device="cuda"),
+                    st_out=torch.zeros_like(st_in))
+
+    src = E.pool_of(pool.view(L, 2, n_src, page, H, d))
+    spt, dpt = dev(src_pt), dev(dst_pt)
+    a, s = outputs(), outputs()
+    n = E.workspace_bytes(cfg, C)
+    ws = torch.full((n,), 0x7F, dtype=torch.uint8, device="cuda")
+    io = E.make_step_io(C, hidden, D, C * D, n_cached, n_prefix, src, spt, src_pt.shape[1],
+                        E.pool_of(a["dst"].view(L, 2, n_dst, page, H, d)), dpt, dst_pt.shape[1],
+                        a["scores"], ld_s, st_in, a["st_out"], a["keep"], a["nk"], a["status"],
+                        ws, n, dst_scores=a["dsc"], src_pos=pos, dst_pos=a["dpos"])
+    E.epikv_evict_step(cfg, io)
+    sig = torch.zeros((na + nb, B, C), device="cuda")
+    E.epikv_score(cfg, C, hidden, D, C * D, state_in=st_in, state_out=s["st_out"], sig=sig)
+    E.epikv_zscore(cfg, C, sig, n_cached, st_in, s["st_out"], s["scores"], ld_s)
+    E.epikv_select(cfg, s["scores"], ld_s, n_cached, n_prefix, s["keep"], s["nk"], s["status"])
+    # (the step refuses a sequence shorter than its chunk; select alone does not)
+    short = torch.from_numpy(lengths < C).cuda()
+    s["nk"][short] = -1
+    s["status"][short] = E.SEQ_RANGE
+    s["keep"][short] = -5
+    m = E.compact_workspace_bytes(cfg)
+    cws = torch.full((m,), 0x7F, dtype=torch.uint8, device="cuda")
+    E.epikv_compact(cfg, src, spt, src_pt.shape[1],
+                    E.pool_of(s["dst"].view(L, 2, n_dst, page, H, d)), dpt, dst_pt.shape[1],
+                    s["keep"], s["nk"], s["scores"], s["dsc"], pos, s["dpos"], ld_s, s["status"],
+                    cws, m)
+    torch.cuda.synchronize()
+    for k in a:
+        assert np.array_equal(host(a[k]), host(s[k])), k
+    status = host(a["status"])
+    assert status[-1] == E.SEQ_BUDGET
+    if bad:
+        assert list(status[:3]) == [E.SEQ_RANGE] * 3
