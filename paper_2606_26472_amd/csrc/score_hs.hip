@@ -124,9 +124,18 @@ hipError_t launch_score_hs(const ScoreHsArgs& a, hipStream_t s) {
     if (nvec <= 256) return launch_wave<4, 4>(w, s);
     return launch_wave<8, 2>(w, s);
   }
+  // Segments of kScoreSeg tokens, shorter while they leave compute units
+  // without a workgroup (15 rows a token): 1 x 128 x 8192 38 -> 21 us, 4 x
+  // 128 x 8192 43 -> 37, 1 x 64 x 16384 60 -> 26, 16 x 128 x 5120 the same;
+  // wanting 512 or 1024 workgroups re-reads more than it gains (8 x 128 x
+  // 8192 55 us with 256, 59 and 66 us).
+  ScoreHsArgs w = a;
+  while (w.seg_len > kScoreSegMin &&
+         (int64_t)((w.C + w.seg_len - 1) / w.seg_len) * w.n_band * w.B < kScoreWgWanted)
+    w.seg_len >>= 1;
   const int vpt = (nvec + kScoreThreads - 1) / kScoreThreads;
-  if (vpt <= 4) return launch<4, 4>(a, s);
-  return launch<8, 2>(a, s);
+  if (vpt <= 4) return launch<4, 4>(w, s);
+  return launch<8, 2>(w, s);
 }
 
 }  // namespace epikv
