@@ -32,7 +32,7 @@ PROBE_SOURCES = ["copy_probe.hip"]
 
 SOURCES = ["epikv_api.hip", "score_hs.hip", "score_lagkv.hip", "zscore.hip",
            "select.hip", "compact.hip", "compact_inplace.hip", "score_tokens.hip",
-           "smooth_resolve.hip",
+           "smooth_resolve.hip", "step_prep.hip",
            "score_select.hip", "select_multi.hip", "noalloc.hip"]
 
 ARCH = "gfx950"

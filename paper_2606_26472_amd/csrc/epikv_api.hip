@@ -304,7 +304,8 @@ int run_score(const epikv_cfg* c, int32_t chunk, const void* const* hidden, int6
   ScoreLagArgs a;
   LagReduceArgs r;
   lag_args(c, chunk, pool, pt, ld_pt, n_cached, state_in, state_out, sig, partial, &a, &r);
-  return launched(launch_score_lagkv(a, r, s));
+  const hipError_t e = launch_score_lagkv(a, s);
+  return launched(e == hipSuccess ? launch_lag_reduce(r, s) : e);
 }
 
 int check_score_tokens(const epikv_cfg* c, int32_t chunk, const void* const* hidden,
@@ -729,7 +730,8 @@ EPIKV_EXPORT int epikv_select(const epikv_cfg* cfg, const float* scores, int64_t
   const int st = check_select(cfg, scores, ld_s, n_cached, n_prefix, keep_idx, n_keep, seq_status);
   if (st) return st;
   return launched(launch_select(
-      select_args(cfg, scores, ld_s, n_cached, n_prefix, keep_idx, n_keep, seq_status, 0), stream));
+      select_args(cfg, scores, ld_s, n_cached, n_prefix, keep_idx, n_keep, seq_status, 0), nullptr,
+      stream));
 }
 
 EPIKV_EXPORT size_t epikv_select_workspace_bytes(const epikv_cfg* cfg) {
@@ -753,7 +755,8 @@ EPIKV_EXPORT int epikv_select_ws(const epikv_cfg* cfg, const float* scores, int6
   }
   const SelectArgs a =
       select_args(cfg, scores, ld_s, n_cached, n_prefix, keep_idx, n_keep, seq_status, 0);
-  return launched(need > 0 ? launch_select_groups(a, workspace, stream) : launch_select(a, stream));
+  return launched(need > 0 ? launch_select_groups(a, workspace, false, nullptr, stream)
+                           : launch_select(a, nullptr, stream));
 }
 
 EPIKV_EXPORT int epikv_compact(const epikv_cfg* cfg, const epikv_pool* src, const int32_t* src_pt,
@@ -874,11 +877,7 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
                       io->ld_dst_pt, io->keep_idx, io->n_keep, src_scores, io->dst_scores,
                       io->src_pos, io->dst_pos, io->ld_s, io->seq_status, ws_offsets);
   bool selected = false;  // the select stage is on the stream
-  if (!scoring) {
-    st = launched(launch_select_groups(sel, ws_select, stream));
-    if (st) return st;
-    selected = true;
-  } else if (cfg->signal == EPIKV_SIGNAL_HS) {
+  if (scoring && cfg->signal == EPIKV_SIGNAL_HS) {
     const ScoreHsArgs hs =
         hs_args(cfg, io->chunk, io->hidden, io->ld_tok, io->ld_seq, io->state_in, io->state_out, sig);
     if (select_score_fusable(sel, hs)) {
@@ -898,12 +897,25 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
     }
   }
   if (!selected) {
-    st = run_score(cfg, io->chunk, io->hidden, io->ld_tok, io->ld_seq, &io->src, io->src_pt,
-                   io->ld_src_pt, io->n_cached, io->state_in, io->state_out, sig, partial, stream);
-    if (st) return st;
-    st = launched(launch_zscore(zs, stream));
-    if (st) return st;
-    st = launched(launch_select_groups(sel, ws_select, stream));
+    if (scoring && cfg->signal != EPIKV_SIGNAL_HS && step_prep_reduces(zs)) {
+      ScoreLagArgs la;
+      LagReduceArgs red;
+      lag_args(cfg, io->chunk, &io->src, io->src_pt, io->ld_src_pt, io->n_cached, io->state_in,
+               io->state_out, sig, partial, &la, &red);
+      st = launched(launch_score_lagkv(la, stream));
+      if (st) return st;
+      st = launched(launch_step_prep(zs, &red, sel, ws_select, stream));
+      if (st) return st;
+    } else if (scoring) {
+      st = run_score(cfg, io->chunk, io->hidden, io->ld_tok, io->ld_seq, &io->src, io->src_pt,
+                     io->ld_src_pt, io->n_cached, io->state_in, io->state_out, sig, partial,
+                     stream);
+      if (st) return st;
+      st = launched(launch_step_prep(zs, nullptr, sel, ws_select, stream));
+      if (st) return st;
+    }
+    // (the prep launch has cleared the selection's scratch)
+    st = launched(launch_select_groups(sel, ws_select, scoring, io->in_place ? nullptr : &ca, stream));
     if (st) return st;
   }
   if (io->in_place) {
@@ -913,5 +925,6 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
     if (io->in_place == EPIKV_COMPACT_REMAP) a = remap_args(a, const_cast<int32_t*>(io->src_pt));
     return launched(launch_compact_inplace(a, stream));
   }
-  return launched(launch_compact(ca, stream));
+  st = launched(launch_compact_resolve(ca, stream));
+  return st ? st : launched(launch_compact_gather(ca, stream));
 }

@@ -27,6 +27,14 @@ __device__ __forceinline__ void st_stream(void* p, u32x4 v) {
 constexpr int kBufferRsrcWord3 = 0x00020000;
 constexpr int kBufferNonTemporal = 2;
 
+// IEEE minimum / maximum: a NaN propagates.
+__device__ __forceinline__ float nan_min(float a, float b) {
+  return __builtin_elementwise_minimum(a, b);
+}
+__device__ __forceinline__ float nan_max(float a, float b) {
+  return __builtin_elementwise_maximum(a, b);
+}
+
 // Sum over the 64 lanes of a wavefront with a fixed butterfly order, so the
 // result is identical on every lane and from run to run.
 __device__ __forceinline__ float wave_sum(float v) {
@@ -274,14 +282,19 @@ __device__ __forceinline__ float band_combine(const float (*vals)[TILE], int t, 
 int device_cus();
 hipError_t launch_score_hs(const ScoreHsArgs& a, hipStream_t s);
 hipError_t launch_score_tokens(const ScoreTokArgs& a, hipStream_t s);
-hipError_t launch_score_lagkv(const ScoreLagArgs& a, const LagReduceArgs& r,
-                              hipStream_t s);
+hipError_t launch_score_lagkv(const ScoreLagArgs& a, hipStream_t s);
+hipError_t launch_lag_reduce(const LagReduceArgs& r, hipStream_t s);
 hipError_t launch_zscore(const ZscoreArgs& a, hipStream_t s);
-hipError_t launch_select(const SelectArgs& a, hipStream_t s);
+hipError_t launch_select(const SelectArgs& a, const CompactArgs* ca, hipStream_t s);
 // The eviction step's selection: several workgroups per sequence when the
 // batch is too small to fill the device with one each (scratch of
-// select_scratch_bytes(B), kept between calls), else launch_select.
-hipError_t launch_select_groups(const SelectArgs& a, void* scratch, hipStream_t s);
+// select_scratch_bytes(B), made clear by a launch before the selection's
+// unless `cleared` says that it is), else launch_select.  With `ca`, one more
+// workgroup runs the order stage of that rebuild.
+hipError_t launch_select_groups(const SelectArgs& a, void* scratch, bool cleared,
+                                const CompactArgs* ca, hipStream_t s);
+// Words of scratch to clear for that selection (0: it is not split).
+int64_t select_clear_words(const SelectArgs& a, const void* scratch);
 size_t select_scratch_bytes(int B);
 // Selection and hidden-state scoring in one launch; valid only when
 // select_score_fusable (the chunk lies inside the recency window).
@@ -292,6 +305,13 @@ hipError_t launch_select_score(const SelectArgs& sel, const ScoreHsArgs& sc, con
 // Smoothing and, for a step whose selection is on the stream and whose chunk
 // it keeps whole, the resolve stage of an out-of-place rebuild.
 hipError_t launch_smooth_resolve(const ZscoreArgs& a, const CompactArgs& ca, hipStream_t s);
+// The small stages that a step needs before its selection, in one launch:
+// the smoothing, for a KV-vector signal with the reduction of its planes
+// (red; null: the signal is there), and the clearing of the selection's
+// scratch.
+bool step_prep_reduces(const ZscoreArgs& zs);  // it can take the reduction
+hipError_t launch_step_prep(const ZscoreArgs& zs, const LagReduceArgs* red, const SelectArgs& sel,
+                            void* scratch, hipStream_t s);
 hipError_t launch_compact(const CompactArgs& a, hipStream_t s);  // its three stages
 hipError_t launch_compact_order(const CompactArgs& a, hipStream_t s);
 hipError_t launch_compact_resolve(const CompactArgs& a, hipStream_t s);

@@ -53,7 +53,7 @@
 // partial[b][plane][segment][c].
 // Kernel 2 sums the planes in a fixed order and divides by L*H, and (split
 // rows) combines the splits' channel ranges into the next chunk's reference.
-#include "epikv_internal.h"
+#include "lag_reduce_impl.h"
 
 namespace epikv {
 namespace {
@@ -133,13 +133,6 @@ __device__ __forceinline__ void ld_lane_nt(const char* p, uint32_t (&w)[NW]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) w[4 * c + k] = v[k];
   }
-}
-
-__device__ __forceinline__ float nan_min(float a, float b) {
-  return __builtin_elementwise_minimum(a, b);
-}
-__device__ __forceinline__ float nan_max(float a, float b) {
-  return __builtin_elementwise_maximum(a, b);
 }
 
 // LAG: lag-normalised signal.  NW: words (2 * NW channels) per lane.
@@ -698,57 +691,31 @@ __global__ __launch_bounds__(kFirstThreads) void k_lag_first_range(ScoreLagArgs 
   }
 }
 
-// Blocks [0, tok_blocks) of each sequence: q(t) = the sum of token t's
-// partial sums over the used planes and row segments, times 1/(L*H).  A
-// block takes kRedTok tokens; its kScoreThreads / kRedTok parts each add
-// every parts-th partial in order, then the parts are added in order.  The
-// remaining blocks (split rows of a lag-normalised signal): each channel's
-// range over the chunk = the min and max of the shares' partial ranges, in
-// a fixed order.
-constexpr int kRedTok = 64;
-constexpr int kRedParts = kScoreThreads / kRedTok;
+// Blocks [0, tok_blocks) of each sequence: q(t) of kRedTok tokens; the
+// remaining blocks (split rows of a lag-normalised signal): the channels'
+// ranges over the chunk (lag_reduce_impl.h).
+constexpr int kRedTok = kScoreThreads / kLagRedParts;
 
 __global__ __launch_bounds__(kScoreThreads) void k_lag_reduce(LagReduceArgs a) {
-  __shared__ float red[kRedParts][kRedTok];
+  __shared__ float red[kLagRedParts][kRedTok];
   const int b = blockIdx.y;
   const int tok_blocks = (a.C + kRedTok - 1) / kRedTok;
   if ((int)blockIdx.x < tok_blocks) {
     const int t = threadIdx.x % kRedTok;
     const int part = threadIdx.x / kRedTok;
     const int c = blockIdx.x * kRedTok + t;
-    float s = 0.f;
-    if (c < a.C) {
-      const float* p = a.partial + (int64_t)b * a.n_sums * a.C + c;
-#pragma unroll 16
-      for (int pl = part; pl < a.n_sums; pl += kRedParts) s += p[(int64_t)pl * a.C];
-    }
-    red[part][t] = s;
+    red[part][t] = c < a.C ? lag_reduce_impl::part_sum(a, b, c, part) : 0.f;
     __syncthreads();
     if (part == 0 && c < a.C) {
       float q = red[0][t];
 #pragma unroll
-      for (int k = 1; k < kRedParts; ++k) q += red[k][t];
+      for (int k = 1; k < kLagRedParts; ++k) q += red[k][t];
       a.sig[(int64_t)b * a.C + c] = q * a.inv_count;
     }
     return;
   }
   const int i = ((int)blockIdx.x - tok_blocks) * kScoreThreads + threadIdx.x;
-  if (i >= a.n_chan) return;
-  const int64_t half = (int64_t)a.B * a.n_chan;
-  const int64_t o = (int64_t)b * a.n_chan + i;
-  const int kv = (i / (a.n_chan / (2 * a.L))) & 1;
-  float lo = 0.f, hi = 0.f;  // planes of an unused tensor carry no range
-  if (kv == 0 ? a.use_k : a.use_v) {
-    lo = a.prange[o];
-    hi = a.prange[half + o];
-#pragma unroll 4
-    for (int sp = 1; sp < a.splits; ++sp) {
-      lo = nan_min(lo, a.prange[sp * 2 * half + o]);
-      hi = nan_max(hi, a.prange[sp * 2 * half + half + o]);
-    }
-  }
-  a.range_out[o] = lo;
-  a.range_out[half + o] = hi;
+  if (i < a.n_chan) lag_reduce_impl::chunk_range(a, b, i);
 }
 
 template <bool LAG, bool WIDE, int NW, bool RT = false, bool BIG = false>
@@ -770,7 +737,7 @@ size_t lagkv_lds_bytes(int H, int d, bool lag, bool big) {
          kLagPtCache * sizeof(int);
 }
 
-hipError_t launch_score_lagkv(const ScoreLagArgs& args, const LagReduceArgs& r, hipStream_t s) {
+hipError_t launch_score_lagkv(const ScoreLagArgs& args, hipStream_t s) {
   ScoreLagArgs a = args;
   a.first_split = a.lag && a.splits > 1 &&
                   (int64_t)a.n_planes * a.B * a.C * (a.H * a.d * 2) >= kLagFirstBytes;
@@ -795,7 +762,10 @@ hipError_t launch_score_lagkv(const ScoreLagArgs& args, const LagReduceArgs& r, 
             : (!wide ? launch_lag<false, false, kLagWords>(a, s)
                : rt  ? launch_lag<false, true, kLagWords, true>(a, s)
                      : launch_lag<false, true, kLagWords>(a, s));
-  if (e != hipSuccess) return e;
+  return e;
+}
+
+hipError_t launch_lag_reduce(const LagReduceArgs& r, hipStream_t s) {
   const int tok_blocks = (r.C + kRedTok - 1) / kRedTok;
   const int rng_blocks = r.lag && r.splits > 1 ? (r.n_chan + kScoreThreads - 1) / kScoreThreads : 0;
   hipLaunchKernelGGL(k_lag_reduce, dim3(tok_blocks + rng_blocks, r.B), dim3(kScoreThreads), 0, s,

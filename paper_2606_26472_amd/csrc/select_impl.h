@@ -135,6 +135,13 @@ __device__ __forceinline__ void find_digit(const uint32_t* hist, int nb, uint32_
   }
 }
 
+// Word i of the split selection's scratch as it has to be when the selection
+// starts: a sequence's head words zero but for the marker, histograms zero.
+__device__ __forceinline__ void clear_scratch_word(uint32_t* scratch, int64_t i) {
+  const int64_t w = i % kSelSeqWords;
+  scratch[i] = w == 0 ? kSelMarkLo : (w == 1 ? kSelMarkHi : 0u);
+}
+
 // Rows kept of sequence b, or negative if it is refused: all that the counts
 // say before any score is looked at.
 __device__ __forceinline__ int expected_keep(const SelectArgs& a, int b) {

@@ -33,7 +33,8 @@
 // to the known total has every word final.
 //
 // Each sequence's scratch therefore has to be clear when the kernel starts.
-// A small fill kernel launched just before it writes every sequence's block
+// A launch just before it (a small fill kernel, or the step's own launch of
+// its small stages) writes every sequence's block
 // (histograms and flags zero, a 64-bit marker that the block is clear), so
 // nothing depends on what the workspace held before: it may have served
 // another batch size's layout, or other data, since the previous call.
@@ -42,12 +43,16 @@
 // found without the marker is cleared by the sequence's last workgroup,
 // which then sets it, while the others wait.)
 //
-// The launcher keeps the grid within one workgroup per compute unit, so all
+// With ORDER one more workgroup ranks the destination pages of the step's
+// out-of-place rebuild, for which the counts suffice (compact_impl.h).
+//
+// The launcher keeps the selection within one workgroup per compute unit, so all
 // of a sequence's workgroups can run together; should they not (other work
 // holding the device), a waiting workgroup gives up after about a second,
 // the sequence is flagged EPIKV_SEQ_SYNC and every wave still ends.
 #include <atomic>
 
+#include "compact_impl.h"
 #include "select_impl.h"
 
 namespace epikv {
@@ -191,14 +196,20 @@ __device__ __forceinline__ void find_digit_wave(const uint32_t* hist, uint32_t n
   }
 }
 
-template <int KPT>
-__global__ __launch_bounds__(kSelectThreads) void k_select_multi(SelectMultiArgs m) {
+template <int KPT, bool ORDER>
+__global__ __launch_bounds__(kSelectThreads) void k_select_multi(SelectMultiArgs m,
+                                                                 CompactArgs ca) {
   __shared__ __align__(16) uint32_t hist[2048];
   __shared__ uint32_t tab[2][KPT * kWaves];  // per (row of 1024, wavefront) counts
   __shared__ uint32_t wtot[2][kWaves];
   __shared__ uint32_t bcast[8];
   const SelectArgs& a = m.sel;
   const int G = m.groups;
+  if (ORDER && (int)blockIdx.x == a.B * G) {
+    // (the last workgroup to start; no other waits for it)
+    compact_impl::order_pages(ca, [&](int b) { return select_impl::expected_keep(a, b); });
+    return;
+  }
   const int b = (int)blockIdx.x / G;
   const int g = (int)blockIdx.x - b * G;
   const int tid = threadIdx.x;
@@ -485,22 +496,42 @@ __global__ __launch_bounds__(kSelectThreads) void k_select_multi(SelectMultiArgs
 }
 
 template <int KPT>
-hipError_t launch(const SelectMultiArgs& m, hipStream_t s) {
-  hipLaunchKernelGGL((k_select_multi<KPT>), dim3((unsigned)(m.sel.B * m.groups)),
-                     dim3(kSelectThreads), 0, s, m);
+hipError_t launch(const SelectMultiArgs& m, const CompactArgs* ca, hipStream_t s) {
+  const unsigned n = (unsigned)(m.sel.B * m.groups);
+  if (ca)
+    hipLaunchKernelGGL((k_select_multi<KPT, true>), dim3(n + 1), dim3(kSelectThreads), 0, s, m, *ca);
+  else
+    hipLaunchKernelGGL((k_select_multi<KPT, false>), dim3(n), dim3(kSelectThreads), 0, s, m,
+                       CompactArgs());
   return hipGetLastError();
 }
 
 constexpr size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// Every sequence's scratch block made clear before the selection: head
-// words zero but for the marker, histograms zero.  One thread per word of
-// the first n_words words (the B sequences' blocks).
+// Every sequence's scratch block made clear before the selection: one thread
+// per word of the first n_words words (the B sequences' blocks).
 __global__ __launch_bounds__(256) void k_select_scratch_clear(uint32_t* scratch, int64_t n_words) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_words) return;
-  const int64_t w = i % kSelSeqWords;
-  scratch[i] = w == 0 ? kSelMarkLo : (w == 1 ? kSelMarkHi : 0u);
+  if (i < n_words) select_impl::clear_scratch_word(scratch, i);
+}
+
+// The fewest keys per thread (1, 2, 4, 8 or 16, as a power of two; 32 would
+// spill) whose grid fits one workgroup per compute unit, so that a sequence's
+// workgroups all run together (always resident, and measured faster than
+// sharing units between two); -1 if the selection is not split.
+int split_keys(const SelectArgs& a, const void* scratch, int* groups) {
+  const int64_t cap = min(kSelMaxGrid, device_cus());
+  if (!scratch || select_scratch_bytes(a.B) == 0) return -1;
+  for (int j = 0; j < 5; ++j) {
+    const int64_t span = (int64_t)(1 << j) * kSelectThreads;
+    const int64_t G = (a.ld_s + span - 1) / span;
+    if (G < 2) break;  // one workgroup covers the row: nothing to split
+    if ((int64_t)a.B * G <= cap) {
+      *groups = (int)G;
+      return j;
+    }
+  }
+  return -1;
 }
 
 }  // namespace
@@ -525,47 +556,39 @@ size_t select_scratch_bytes(int B) {
   return align256((size_t)B * kSelSeqWords * 4 + (size_t)kSelMaxGrid * 8);
 }
 
-hipError_t launch_select_groups(const SelectArgs& a, void* scratch, hipStream_t s) {
-  // The fewest keys per thread (1, 2, 4, 8 or 16; 32 would spill) whose
-  // grid fits one workgroup per compute unit, so that a sequence's
-  // workgroups all run together (always resident, and measured faster than
-  // sharing units between two).
-  int v = -1, groups = 1;
-  const int64_t cap = min(kSelMaxGrid, device_cus());
-  if (scratch && select_scratch_bytes(a.B) > 0) {
-    for (int j = 0; j < 5; ++j) {
-      const int64_t span = (int64_t)(1 << j) * kSelectThreads;
-      const int64_t G = (a.ld_s + span - 1) / span;
-      if (G < 2) break;  // one workgroup covers the row: nothing to split
-      if ((int64_t)a.B * G <= cap) {
-        v = j;
-        groups = (int)G;
-        break;
-      }
-    }
-  }
-  if (v < 0) return launch_select(a, s);
+int64_t select_clear_words(const SelectArgs& a, const void* scratch) {
+  int groups;
+  return split_keys(a, scratch, &groups) < 0 ? 0 : (int64_t)a.B * kSelSeqWords;
+}
 
-  // The scratch is cleared here rather than trusted to be as the previous
-  // call left it: a workspace may have held other data since (another
-  // batch size's layout, or the caller's own use), and a stale count would
-  // leave a histogram that never adds up.
-  const int64_t n_words = (int64_t)a.B * kSelSeqWords;
-  hipLaunchKernelGGL(k_select_scratch_clear, dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0, s,
-                     (uint32_t*)scratch, n_words);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+hipError_t launch_select_groups(const SelectArgs& a, void* scratch, bool cleared,
+                                const CompactArgs* ca, hipStream_t s) {
+  int groups = 1;
+  const int v = split_keys(a, scratch, &groups);
+  if (v < 0) return launch_select(a, ca, s);
+
+  // The scratch is cleared on every call rather than trusted to be as the
+  // previous one left it: a workspace may have held other data since
+  // (another batch size's layout, or the caller's own use), and a stale
+  // count would leave a histogram that never adds up.
+  if (!cleared) {
+    const int64_t n_words = (int64_t)a.B * kSelSeqWords;
+    hipLaunchKernelGGL(k_select_scratch_clear, dim3((unsigned)((n_words + 255) / 256)), dim3(256), 0,
+                       s, (uint32_t*)scratch, n_words);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
 
   SelectMultiArgs m;
   m.sel = a;
   m.scratch = (uint32_t*)scratch;
   m.groups = groups;
   switch (v) {
-    case 0: return launch<1>(m, s);
-    case 1: return launch<2>(m, s);
-    case 2: return launch<4>(m, s);
-    case 3: return launch<8>(m, s);
-    default: return launch<16>(m, s);
+    case 0: return launch<1>(m, ca, s);
+    case 1: return launch<2>(m, ca, s);
+    case 2: return launch<4>(m, ca, s);
+    case 3: return launch<8>(m, ca, s);
+    default: return launch<16>(m, ca, s);
   }
 }
 

@@ -52,7 +52,8 @@ __global__ __launch_bounds__(kZscoreThreads) void k_smooth_resolve(ZscoreArgs a,
   if (EMA)
     zscore_impl::ema_tiles(a, t, per, b, put);
   else
-    zscore_impl::zscore_tile(a, t, tiles_seq, b, put);
+    zscore_impl::zscore_tile(
+        a, t, tiles_seq, b, [&](int l, int c) { return zscore_impl::read_sig(a, b, l, c); }, put);
 }
 
 }  // namespace

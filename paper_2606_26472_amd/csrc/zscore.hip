@@ -6,10 +6,10 @@ namespace epikv {
 namespace {
 
 __global__ __launch_bounds__(kZscoreThreads) void k_zscore(ZscoreArgs a) {
-  zscore_impl::zscore_tile(a, blockIdx.x, gridDim.x, blockIdx.y,
-                           [&](int b, int c, int N, float s) {
-                             zscore_impl::put_score(a, b, c, N, s);
-                           });
+  const int b = blockIdx.y;
+  zscore_impl::zscore_tile(
+      a, blockIdx.x, gridDim.x, b, [&](int l, int c) { return zscore_impl::read_sig(a, b, l, c); },
+      [&](int b, int c, int N, float s) { zscore_impl::put_score(a, b, c, N, s); });
 }
 
 __global__ __launch_bounds__(kZscoreThreads) void k_ema(ZscoreArgs a, int per) {

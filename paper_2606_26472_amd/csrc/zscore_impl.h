@@ -25,11 +25,12 @@ namespace zscore_impl {
 constexpr int kWaves = kZscoreThreads / 64;
 constexpr int kSlice = EPIKV_MAX_WINDOW - 1 + kZscoreTile;
 
-// Tile `tile` of the n_tiles of sequence b.  put(b, c, N, s) receives each
-// token's score, when the sequence's row has room for the chunk.
-template <typename Put>
+// Tile `tile` of the n_tiles of sequence b.  sig(l, c): row l's signal of
+// token c.  put(b, c, N, s) receives each token's score, when the sequence's
+// row has room for the chunk.
+template <typename Sig, typename Put>
 __device__ __forceinline__ void zscore_tile(const ZscoreArgs& a, int tile, int n_tiles, int b,
-                                            Put put) {
+                                            Sig sig, Put put) {
   __shared__ float xs[kWaves][kSlice];
   __shared__ float vals[EPIKV_MAX_BAND][kZscoreTile];
   const int tid = threadIdx.x;
@@ -62,14 +63,13 @@ __device__ __forceinline__ void zscore_tile(const ZscoreArgs& a, int tile, int n
     const bool active = l < a.n_sig;
     if (active) {
       const float* ring = a.ring_in + ((int64_t)b * a.n_sig + l) * wm1;
-      const float* sg = a.sig + ((int64_t)l * a.B + b) * a.C;
       for (int k = lane; k < span; k += 64) {
         const int j = base + k;
         float v = 0.f;
         if (j < wm1)
           v = ring[j];
         else if (j - wm1 < a.C)
-          v = sg[j - wm1];
+          v = sig(l, j - wm1);
         x[k] = v;
       }
     }
@@ -236,6 +236,11 @@ __device__ __forceinline__ void ema_tiles(const ZscoreArgs& a, int blk, int per,
     a.ring_out[((int64_t)b * a.n_sig + l) * wm1 + k] = v;
   }
   if (tid == 0) a.n_tok_out[b] = n_tok + a.C;
+}
+
+// The signal [n_sig][B][C] in memory.
+__device__ __forceinline__ float read_sig(const ZscoreArgs& a, int b, int l, int c) {
+  return a.sig[((int64_t)l * a.B + b) * a.C + c];
 }
 
 // The scores' row of the sequence.
