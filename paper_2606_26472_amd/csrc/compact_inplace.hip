@@ -398,11 +398,6 @@ __device__ __forceinline__ void st_row_nt(char* row, uint32_t off, int n_bytes, 
       __builtin_amdgcn_make_buffer_rsrc((void*)row, (short)0, n_bytes, kBufferRsrcWord3);
   __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, kBufferNonTemporal);
 }
-__device__ __forceinline__ u32x4 ld_row_nt(const char* row, uint32_t off, int n_bytes) {
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc((void*)row, (short)0, n_bytes, kBufferRsrcWord3);
-  return __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kBufferNonTemporal);
-}
 
 template <int NI>
 __global__ __launch_bounds__(kCompactThreads) void k_inplace_walk(InplaceArgs a) {

@@ -92,14 +92,6 @@ __device__ __forceinline__ float group_sum(float v, int width) {
   return v;
 }
 
-// Order of one wavefront's LDS accesses by its own lanes: the hardware
-// keeps them in issue order, the compiler must not move them across this.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Transposed head reduction (rows spanning whole wavefronts): each lane's
 // sum and sum of squares over its channels of a row go to LDS, the rows in
 // flight of kRedRowWords per wavefront; the padding after every 8 lanes

@@ -18,18 +18,29 @@ namespace {
 
 constexpr int kWaves = kZscoreThreads / 64;
 constexpr int kSlice = EPIKV_MAX_WINDOW - 1 + kZscoreTile;
+constexpr int kRing = (EPIKV_MAX_WINDOW - 1 + 63) / 64;  // carried samples per lane
 
-template <int VPW, int U>
+// Bound by latency: at one token per call a workgroup reads 15 rows of 8 KiB
+// and their predecessors, and every load is issued before the first wait, none
+// behind another's value (a fresh stream's predecessor is loaded and dropped,
+// as its count comes with the rows).  Of more tokens R - 1 rows are in flight
+// while one is compared with the row before it, which takes R buffers in turn;
+// the waits are exact because every load is issued, past the chunk an empty
+// one.  A wavefront works on its own rows alone until the bands meet.
+// One token of 1 and 32 sequences (15 rows of 4096): launch 10.3 -> 6.7 us and
+// 12.0 -> 8.7 us, against a chain of count, carried samples, rows and window
+// sums that waited on one another; 8 tokens of 16 sequences 28.0 -> 26.2 us.
+template <int VPW, bool ONE>
 __global__ __launch_bounds__(kZscoreThreads) void k_score_tokens(ScoreTokArgs a) {
+  constexpr int R = ONE ? 2 : VPW == 8 ? 3 : VPW == 4 ? 5 : 8;
   __shared__ float xs[kWaves][kSlice];
   __shared__ float vals[EPIKV_MAX_BAND][kZscoreTile];
-  __shared__ float carry[EPIKV_MAX_BAND];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = blockIdx.x;
   const int wm1 = a.w - 1;
-  const int nvec = a.D >> 3;
+  const int N = a.n_cached[b];
   const int n_tok = max(a.n_tok_in[b], 0);
   // The first token of a fresh stream has no predecessor and no sample.
   const bool fresh = n_tok == 0;
@@ -39,104 +50,107 @@ __global__ __launch_bounds__(kZscoreThreads) void k_score_tokens(ScoreTokArgs a)
   const int vstart = wm1 - cnt + c0;
   const int64_t total_out = prior + (a.C - c0);
   const int cnt_out = (int)min((int64_t)wm1, total_out);
-  const u32x4 zero = {0u, 0u, 0u, 0u};
   const float al = a.alpha, bl = 1.0f - a.alpha;
   float* x = xs[wave];
 
-  const int rounds = (a.n_band + kWaves - 1) / kWaves;
-  for (int rd = 0; rd < rounds; ++rd) {
-    const int l = rd * kWaves + wave;
-    const bool active = l < a.n_band;
-    if (active) {
-      const int64_t row = (int64_t)b * a.n_band + l;
-      // (the carried EMA value is loaded first: it is only used after the
-      // rows, so its latency overlaps theirs)
-      const float ema_c = a.ema_in[row];
-      for (int k = lane; k < wm1; k += 64) x[k] = a.ring_in[row * wm1 + k];
-      // Eq. 1 over the chunk's rows, the previous row in registers
-      const uint16_t* rows = a.hidden[l] + (int64_t)b * a.ld_seq;
-      const uint16_t* prow = a.h_prev_in + row * a.D;
-      u32x4 prev[VPW];
+  for (int l = wave; l < a.n_band; l += kWaves) {
+    const int64_t row = (int64_t)b * a.n_band + l;
+    const uint16_t* rows = a.hidden[l] + (int64_t)b * a.ld_seq;
+    // buffer 0 starts with the row before the chunk, buffer u with row u - 1
+    u32x4 buf[R][VPW];
+    auto load = [&](const uint16_t* p, bool ok, u32x4 (&v)[VPW]) {
+#pragma unroll
+      for (int i = 0; i < VPW; ++i) v[i] = ld_row_nt(p, 16 * (lane + 64 * i), ok ? 2 * a.D : 0);
+    };
+    auto load_row = [&](int c, u32x4 (&v)[VPW]) {
+      load(rows + (c < a.C ? (int64_t)c * a.ld_tok : 0), c < a.C, v);
+    };
+    load(a.h_prev_in + row * a.D, true, buf[0]);
+#pragma unroll
+    for (int u = 1; u < R; ++u) load_row(u - 1, buf[u]);
+    const float* ring_in = a.ring_in + row * wm1;
+    float ring[kRing];
+#pragma unroll
+    for (int k = 0; k < kRing; ++k) ring[k] = ring_in[min(lane + 64 * k, max(wm1 - 1, 0))];
+    const float ema_c = a.ema_in[row];
+    // Eq. 1 over the chunk's rows
+    auto change = [&](int c, const u32x4 (&prev)[VPW], const u32x4 (&cur)[VPW]) {
+      float acc = 0.f;
 #pragma unroll
       for (int i = 0; i < VPW; ++i) {
-        const int v = lane + i * 64;
-        prev[i] = (v < nvec && !fresh) ? ld_stream(prow + v * 8) : zero;
+        acc = sqdiff8(cur[i], prev[i], acc);
+        if (!ONE) __builtin_amdgcn_sched_barrier(0);  // (few unpacked values at a time)
       }
-      for (int c = 0; c < a.C; c += U) {
-        u32x4 cur[U][VPW];
+      const float g2 = wave_sum(acc);
+      if (lane == 0) x[wm1 + c] = (fresh && c == 0) ? 0.f : sqrtf(g2);
+      if (c == a.C - 1) {
+        // the chunk's last row is the next call's predecessor
+        const __amdgpu_buffer_rsrc_t hout = __builtin_amdgcn_make_buffer_rsrc(
+            a.h_prev_out + row * a.D, (short)0, 2 * a.D, kBufferRsrcWord3);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
+        for (int i = 0; i < VPW; ++i)
+          __builtin_amdgcn_raw_buffer_store_b128(cur[i], hout, 16 * (lane + 64 * i), 0, 0);
+      }
+    };
+    if (ONE) {
+      change(0, buf[0], buf[1]);
+    } else {
+#pragma unroll 1
+      for (int cb = 0; cb < a.C; cb += R) {
 #pragma unroll
-          for (int i = 0; i < VPW; ++i) {
-            const int v = lane + i * 64;
-            cur[u][i] = (c + u < a.C && v < nvec)
-                            ? ld_stream(rows + (int64_t)(c + u) * a.ld_tok + v * 8)
-                            : zero;
-          }
+        for (int u = 0; u < R; ++u) {
+          const int c = cb + u;
+          if (c < a.C) change(c, buf[u], buf[(u + 1) % R]);
+          // (the row is unpacked again as the next one's predecessor: its
+          // 8 * VPW values kept instead would spill)
+#pragma unroll
+          for (int i = 0; i < VPW; ++i) asm volatile("" : "+v"(buf[(u + 1) % R][i]));
+          // (not before the rows are used: there are no registers for it)
+          __builtin_amdgcn_sched_barrier(0);
+          load_row(c + R - 1, buf[u]);
+          __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float acc = 0.f;
-#pragma unroll
-          for (int i = 0; i < VPW; ++i)
-            acc = sqdiff8(cur[u][i], u == 0 ? prev[i] : cur[u - 1][i], acc);
-          const float g2 = wave_sum(acc);
-          if (lane == 0 && c + u < a.C)
-            x[wm1 + c + u] = (fresh && c + u == 0) ? 0.f : sqrtf(g2);
-        }
-        // (prev: the latest row of the chunk, so after the loop its last)
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (c + u < a.C)
-#pragma unroll
-            for (int i = 0; i < VPW; ++i) prev[i] = cur[u][i];
       }
-      // the chunk's last row is the next call's predecessor (from registers)
-      uint16_t* hout = a.h_prev_out + row * a.D;
-#pragma unroll
-      for (int i = 0; i < VPW; ++i) {
-        const int v = lane + i * 64;
-        if (v < nvec) *reinterpret_cast<u32x4*>(hout + v * 8) = prev[i];
-      }
-      if (lane == 0) carry[l] = ema_c;
     }
-    __syncthreads();
-    if (active) {
-      const int row = b * a.n_band + l;
-      const int c = lane;
-      const bool has = c < a.C && c >= c0;
-      float v = 0.f;
-      if (a.mode == EPIKV_SMOOTH_EMA) {
-        const float xv = has ? x[wm1 + c] : 0.f;
-        const float y = ema_scan(xv, has, prior == 0 && c == c0, al, bl, carry[l], lane);
-        v = has ? y : 0.f;
-        const float y_last = __shfl(y, 63, 64);
-        if (lane == 0) a.ema_out[row] = y_last;
-      } else {
-        if (has) {
-          const int j = wm1 + c;
-          v = smooth_at(x, 0, max(vstart, j - wm1), j, a.mode, a.eps);
-        }
-        if (lane == 0) a.ema_out[row] = carry[l];
-      }
-      vals[l][lane] = v;
-      // carried samples: the last min(w-1, samples), right-aligned
-      float* ro = a.ring_out + (int64_t)row * wm1;
-      for (int k = lane; k < wm1; k += 64) ro[k] = ((wm1 - 1 - k) < cnt_out) ? x[a.C + k] : 0.f;
+#pragma unroll
+    for (int k = 0; k < kRing; ++k)
+      if (lane + 64 * k < wm1) x[lane + 64 * k] = ring[k];
+    wave_sync();
+
+    const int c = lane;
+    const bool has = c < a.C && c >= c0;
+    float v = 0.f;
+    float ema = ema_c;
+    if (a.mode == EPIKV_SMOOTH_EMA) {
+      const float y = ema_scan(has ? x[wm1 + c] : 0.f, has, prior == 0 && c == c0, al, bl, ema_c,
+                               lane);
+      v = has ? y : 0.f;
+      ema = __shfl(y, 63, 64);
+    } else if (has) {
+      const int j = wm1 + c;
+      v = smooth_at(x, 0, max(vstart, j - wm1), j, a.mode, a.eps);
     }
-    __syncthreads();
+    if (lane == 0) a.ema_out[row] = ema;
+    vals[l][lane] = v;
+    // carried samples: the last min(w-1, samples), right-aligned
+    for (int k = lane; k < wm1; k += 64)
+      a.ring_out[row * wm1 + k] = ((wm1 - 1 - k) < cnt_out) ? x[a.C + k] : 0.f;
+    wave_sync();  // (x is rewritten)
   }
+  __syncthreads();
   if (tid < a.C) {
     const float s = band_combine<kZscoreTile>(vals, tid, a.n_a, a.n_band, a.n_b);
-    const int N = a.n_cached[b];
     if (N >= a.C && (int64_t)N <= a.ld_s) a.scores[(int64_t)b * a.ld_s + (N - a.C) + tid] = s;
   }
   if (tid == 0) a.n_tok_out[b] = n_tok + a.C;
 }
 
-template <int VPW, int U>
+template <int VPW>
 hipError_t launch(const ScoreTokArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_score_tokens<VPW, U>), dim3(a.B), dim3(kZscoreThreads), 0, s, a);
+  if (a.C == 1)
+    hipLaunchKernelGGL((k_score_tokens<VPW, true>), dim3(a.B), dim3(kZscoreThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_score_tokens<VPW, false>), dim3(a.B), dim3(kZscoreThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -144,10 +158,10 @@ hipError_t launch(const ScoreTokArgs& a, hipStream_t s) {
 
 hipError_t launch_score_tokens(const ScoreTokArgs& a, hipStream_t s) {
   const int nvec = a.D / 8;
-  if (nvec <= 64) return launch<1, 4>(a, s);
-  if (nvec <= 128) return launch<2, 2>(a, s);
-  if (nvec <= 256) return launch<4, 2>(a, s);
-  if (nvec <= 512) return launch<8, 1>(a, s);
+  if (nvec <= 64) return launch<1>(a, s);
+  if (nvec <= 128) return launch<2>(a, s);
+  if (nvec <= 256) return launch<4>(a, s);
+  if (nvec <= 512) return launch<8>(a, s);
   return hipErrorInvalidValue;
 }
 
