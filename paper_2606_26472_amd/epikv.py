@@ -7,6 +7,7 @@ built (``python -m paper_2606_26472_amd.build``); there is no fallback.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 
@@ -130,10 +131,10 @@ def lib() -> ctypes.CDLL:
         "epikv_workspace_bytes": (sz, [cfgp, i32]),
         "epikv_compact_workspace_bytes": (sz, [cfgp]),
         "epikv_state_init": (ctypes.c_int, [cfgp, P, P]),
-        "epikv_score": (ctypes.c_int, [cfgp, i32, ctypes.POINTER(P), i64, i64,
+        "epikv_score": (ctypes.c_int, [cfgp, i32, P, i64, i64,
                                        poolp, P, i64, P, P, P, P, P, sz, P]),
         "epikv_zscore": (ctypes.c_int, [cfgp, i32, P, P, P, P, P, i64, P, P]),
-        "epikv_score_tokens": (ctypes.c_int, [cfgp, i32, ctypes.POINTER(P), i64,
+        "epikv_score_tokens": (ctypes.c_int, [cfgp, i32, P, i64,
                                               i64, P, P, P, P, i64, P]),
         "epikv_select": (ctypes.c_int, [cfgp, P, i64, P, P, P, P, P, P]),
         "epikv_select_workspace_bytes": (sz, [cfgp]),
@@ -189,6 +190,9 @@ def _ws(t, nbytes):
 def _stream(stream):
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():
+            # (the handle alone: building a Stream object costs 1 us)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -251,10 +255,19 @@ def epikv_state_init(cfg: Cfg, state, stream=None):
 
 
 def _hidden_array(hidden):
+    """The layers' addresses as a host array (kept alive by the caller)."""
     if hidden is None:
         return None
-    arr = (ctypes.c_void_p * len(hidden))(*[_ptr(h) for h in hidden])
-    return arr
+    # (a packed array: building a ctypes one of 15 addresses took as long as
+    # the rest of the binding's call)
+    try:
+        return array.array("Q", [h.data_ptr() for h in hidden])
+    except AttributeError:
+        return array.array("Q", [_ptr(h) or 0 for h in hidden])
+
+
+def _address(arr):
+    return None if arr is None else arr.buffer_info()[0]
 
 
 def epikv_score(cfg: Cfg, chunk: int, hidden=None, ld_tok=0, ld_seq=0,
@@ -263,7 +276,7 @@ def epikv_score(cfg: Cfg, chunk: int, hidden=None, ld_tok=0, ld_seq=0,
                 workspace=None, workspace_bytes_=0, stream=None):
     arr = _hidden_array(hidden)
     _check(lib().epikv_score(
-        ctypes.byref(cfg), int(chunk), arr, int(ld_tok), int(ld_seq),
+        ctypes.byref(cfg), int(chunk), _address(arr), int(ld_tok), int(ld_seq),
         ctypes.byref(pool) if pool is not None else None, _ptr(page_table),
         int(ld_pt), _ptr(n_cached), _ptr(state_in), _ptr(state_out),
         _ptr(sig), _ws(workspace, workspace_bytes_), int(workspace_bytes_),
@@ -283,7 +296,7 @@ def epikv_score_tokens(cfg: Cfg, chunk: int, hidden, ld_tok, ld_seq, n_cached,
                        state_in, state_out, scores, ld_s, stream=None):
     arr = _hidden_array(hidden)
     _check(lib().epikv_score_tokens(
-        ctypes.byref(cfg), int(chunk), arr, int(ld_tok), int(ld_seq),
+        ctypes.byref(cfg), int(chunk), _address(arr), int(ld_tok), int(ld_seq),
         _ptr(n_cached), _ptr(state_in), _ptr(state_out), _ptr(scores),
         int(ld_s), _stream(stream)), "epikv_score_tokens")
 
@@ -360,7 +373,7 @@ def make_step_io(chunk, hidden, ld_tok, ld_seq, n_cached, n_prefix,
     io.chunk = int(chunk)
     arr = _hidden_array(hidden)
     io._hidden_keepalive = arr
-    io.hidden = ctypes.cast(arr, ctypes.POINTER(ctypes.c_void_p)) \
+    io.hidden = ctypes.cast(_address(arr), ctypes.POINTER(ctypes.c_void_p)) \
         if arr is not None else None
     io.ld_tok, io.ld_seq = int(ld_tok), int(ld_seq)
     io.n_cached, io.n_prefix = _ptr(n_cached), _ptr(n_prefix)
