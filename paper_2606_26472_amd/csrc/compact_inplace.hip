@@ -12,18 +12,16 @@
 //          a plane) to the workspace together with the first hole, and moves
 //          the scores and positions.  A sequence that fails the check is left
 //          untouched and flagged RANGE.
-//   move   one wavefront per (sequence, plane, column slice) walks the moved
-//          slots in ascending order, a tile of T rows at a time (16 to 256,
-//          deeper when there are few walks): it loads the tile's source rows,
-//          waits until every load has returned, then stores them.  A store
-//          to slot j can only overwrite a row that a slot <= j reads; slots
-//          of this tile have read theirs, and slots of later tiles read rows
-//          past the end of this tile (their sources are >= their own slots).
-//          So one wavefront per column slice moves its bytes without any
-//          barrier or second copy, and different slices, planes and
-//          sequences touch disjoint bytes.  With 1 KiB slices the walk is
-//          pipelined: the next tile's loads are in flight while this tile
-//          is stored (they read past every slot written so far).
+//   move   one workgroup per (sequence, plane, column slice) walks the moved
+//          slots in ascending order, a tile of rows at a time: it loads the tile's
+//          source rows, waits until every load has returned, then stores
+//          them.  A store to slot j can only overwrite a row that a slot <= j
+//          reads; slots of this tile have read theirs, and slots of later
+//          tiles read rows past the end of this tile (their sources are >=
+//          their own slots).  So a walk moves its bytes without a second copy, and
+//          different slices, planes and sequences touch disjoint bytes.  The
+//          walk is pipelined: the next tile's loads are in flight while this
+//          tile is stored (they read past every slot written so far).
 //
 // With page remapping (epikv_compact_remap) the check kernel also rewrites
 // the page table so that whole retained pages change places instead of being
@@ -43,12 +41,6 @@ __device__ __forceinline__ void wait_vmem() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0);
   asm volatile("" ::: "memory");
-}
-
-__device__ __forceinline__ int64_t shfl64(int64_t v, int src) {
-  const int lo = __shfl((int)(uint32_t)(uint64_t)v, src);
-  const int hi = __shfl((int)(uint32_t)((uint64_t)v >> 32), src);
-  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
 // Exclusive rank of this thread's flag among the workgroup's set flags (in
@@ -301,188 +293,111 @@ __global__ __launch_bounds__(kInplaceThreads) void k_inplace_check(InplaceArgs a
   }
 }
 
-template <int LPR, int NI>
-__global__ __launch_bounds__(kCompactThreads) void k_inplace_move(InplaceArgs a) {
-  constexpr int RPI = 64 / LPR;          // rows per load instruction
-  constexpr int T = RPI * NI;            // rows per tile
-  constexpr int RPL = (T + 63) / 64;     // records per lane
-  static_assert(T <= 64 || T % 64 == 0, "a tile fills whole record registers");
-  const int lane = threadIdx.x & 63;
-  const int64_t unit = (int64_t)blockIdx.x * kCompactWaves + (threadIdx.x >> 6);
-  const int64_t per_seq = (int64_t)a.n_lk * a.n_slices;
-  const int b = (int)(unit / per_seq);
-  if (b >= a.B) return;
-  const int rem = (int)(unit - (int64_t)b * per_seq);
+// The move: one 1024-thread workgroup per walk,
+// a thread per 16-byte column of a row of the slice, tiles of T rows (eight
+// loads per thread: 64 rows of 2 KiB), software pipelined: tile k + 1's loads
+// are issued before tile k's stores.  This keeps the ordering argument: a
+// tile's stores follow a barrier behind which all of its loads have returned,
+// and tile k + 1 reads positions at or past its own slots, which lie past every
+// slot that tile k (or an earlier one) writes.  One barrier per tile: the
+// records of four tiles are in LDS, written two tiles ahead.
+//
+// Bound by HBM as a walk sees it.  Every load and every store of a full tile
+// is issued on every path, so that a wait is exactly for the tile it needs and
+// never for the stores in between (only the last tile's stores are conditional,
+// and without ALL, where the slice's columns do not divide 1024, those of the
+// threads left over).  A workgroup's tile is one run of 128 KiB where pages are; wavefronts
+// that walked 1 KiB slices by themselves, 2048 of them with 8 rows each, put
+// as many bytes in flight but spread them over 2048 places.
+// Measured, K + 128 -> K and rows of 2 KiB in 64 planes, wavefronts -> this:
+// 16 x 4096 rows 3346 -> 3334 us (5.1 TB/s), 1 x 2000 119 -> 104 us, 1 x 300
+// 21.1 -> 17.0 us, 3 x 700 113.7 -> 110.5 us; rows of 256 bytes (16 x 4096)
+// 438 -> 428 us; of 1536, 768 and 1280 bytes (1 x 2000, 2 x 1000, 4 x 600 rows;
+// their last slices of a row were part empty) 111.5 -> 81.3, 58.2 -> 38.3 and
+// 94.5 -> 81.4 us.  Large batches stay at 5.1 TB/s however they are cut: a
+// plain copy with its destination 256 KiB ahead of its source in the same
+// buffer runs at 4.7 to 5.9 TB/s with the distance between the two, and here
+// that distance grows along the walk.
+constexpr int kTileThreads = 1024;
+constexpr int kTileLoads = 8;
+typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
+
+template <bool ALL>
+__global__ __launch_bounds__(kTileThreads) void k_inplace_tile(InplaceArgs a) {
+  extern __shared__ __align__(16) i64x2 recs[];  // [4][T] (src, dst)
+  const int tid = threadIdx.x;
+  const int rpi = kTileThreads / a.slice_vec;  // rows per load
+  const int T = rpi * kTileLoads;              // (at most kTileThreads)
+  const int per_seq = a.n_lk * a.n_slices;
+  const int b = blockIdx.x / per_seq;
+  const int rem = blockIdx.x - b * per_seq;
   const int pl = rem / a.n_slices;
   const int sl = rem - pl * a.n_slices;
   const int h = a.info[2 * b];
-  const int nk = a.info[2 * b + 1];
-  if (h >= nk) return;
-  const int col = sl * LPR + lane % LPR;
-  const bool col_ok = col < (a.row_bytes >> 4);
-  const int rsub = lane / LPR;
-  char* base = a.pool + (int64_t)(pl >> 1) * a.s_layer + (int64_t)(pl & 1) * a.s_kv + (int64_t)col * 16;
-  const int64_t* rec = a.offsets + 2 * (int64_t)b * a.K;
-  // register r of lane i holds the record of the tile's row r * 64 + i
-  int64_t rs[RPL], rd[RPL];
+  const int n = a.info[2 * b + 1] - h;
+  if (n <= 0) return;
+  int sub = tid / a.slice_vec;
+  const int col = sl * a.slice_vec + tid - sub * a.slice_vec;
+  const bool act = ALL || sub < rpi;
+  if (!act) sub = 0;
+  char* base = a.pool + (int64_t)(pl >> 1) * a.s_layer + (int64_t)(pl & 1) * a.s_kv +
+               (int64_t)col * 16;
+  const i64x2* rec = reinterpret_cast<const i64x2*>(a.offsets) + (int64_t)b * a.K + h;
+  // record `tid` of tile k (past the last: the walk's first, never used)
+  auto load_rec = [&](int k) -> i64x2 {
+    const int64_t j = (int64_t)k * T + tid;
+    return rec[tid < T && j < n ? j : 0];
+  };
+  auto put_rec = [&](int k, i64x2 r) {
+    if (tid < T) recs[(k & 3) * T + tid] = r;
+  };
+  auto load_tile = [&](int k, u32x4 (&v)[kTileLoads]) {
 #pragma unroll
-  for (int r = 0; r < RPL; ++r) {
-    const int t = r * 64 + lane;
-    rs[r] = rd[r] = -1;
-    if (t < T && h + t < nk) {
-      rs[r] = rec[2 * (h + t)];
-      rd[r] = rec[2 * (h + t) + 1];
+    for (int i = 0; i < kTileLoads; ++i) {
+      const int64_t off = recs[(k & 3) * T + i * rpi + sub].x;
+      v[i] = ld_stream(base + (act ? off : 0));  // (left over: the plane's first row)
     }
-  }
-  // (waiting here too keeps the loop head free of a wait for the previous
-  // tile's stores)
-  wait_vmem();
-  for (int j0 = h; j0 < nk; j0 += T) {
-    u32x4 v[NI];
-    int64_t dd[NI];
+  };
+  // every wavefront's loads of this tile have returned
+  auto tile_loaded = [&](u32x4 (&v)[kTileLoads]) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      // row i * RPI + rsub of the tile; RPI divides 64, so its register is
-      // known at compile time
-      const int r = (i * RPI) / 64;
-      const int src = (i * RPI) % 64 + rsub;
-      const int64_t s = shfl64(rs[r], src);
-      dd[i] = shfl64(rd[r], src);
-      if (s >= 0 && col_ok) v[i] = ld_stream(base + s);
-    }
-    // next tile's records, while this tile's rows are in flight
-    int64_t ns[RPL], nd[RPL];
+    for (int i = 0; i < kTileLoads; ++i) asm volatile("" : "+v"(v[i]));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the records written are in LDS
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  put_rec(0, load_rec(0));
+  put_rec(1, load_rec(1));
+  i64x2 next = load_rec(2);
+  __syncthreads();
+  u32x4 va[kTileLoads], vb[kTileLoads];
+  load_tile(0, va);
+  // tile k is in `cur`; returns false after the last
+  auto step = [&](int k, u32x4 (&cur)[kTileLoads], u32x4 (&nxt)[kTileLoads]) -> bool {
+    const int64_t left = n - (int64_t)k * T;
+    if (left <= T) {
+      tile_loaded(cur);
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      const int t = r * 64 + lane;
-      const int jn = j0 + T + t;
-      ns[r] = nd[r] = -1;
-      if (t < T && jn < nk) {
-        ns[r] = rec[2 * jn];
-        nd[r] = rec[2 * jn + 1];
+      for (int i = 0; i < kTileLoads; ++i) {
+        const int row = i * rpi + sub;
+        if (act && row < left) st_stream(base + recs[(k & 3) * T + row].y, cur[i]);
       }
+      return false;
     }
-    wait_vmem();
+    load_tile(k + 1, nxt);
+    put_rec(k + 2, next);  // (over tile k - 2's, last read before two barriers)
+    next = load_rec(k + 3);
+    tile_loaded(cur);
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
-      if (dd[i] >= 0 && col_ok) st_stream(base + dd[i], v[i]);
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-      rs[r] = ns[r];
-      rd[r] = nd[r];
-    }
+    for (int i = 0; i < kTileLoads; ++i)
+      if (act) st_stream(base + recs[(k & 3) * T + i * rpi + sub].y, cur[i]);
+    return true;
+  };
+  for (int k = 0;; k += 2) {
+    if (!step(k, va, vb)) break;
+    if (!step(k + 1, vb, va)) break;
   }
-}
-
-// The move for 1 KiB column slices (64 lanes per row, one row per
-// instruction), software pipelined: tile k + 1's loads are issued before
-// tile k's stores, and a tile's stores wait only for its own loads.  This
-// keeps the ordering argument: tile k + 1 reads positions at or past its
-// own slots, which lie past every slot tile k (or any earlier tile)
-// writes, and tile k's stores follow its loads.  Every load and store is
-// issued, a missing row or record through an empty buffer resource (its
-// loads read 0 without a memory access, its stores are dropped), so that
-// the operations in flight are the same on every path and each wait is
-// exactly for the tile it needs.
-// One (src, dst) record per lane for the rows of a tile: lane t < NI holds
-// the tile's row t (a lane past the walk's rows loads the first record
-// and is marked absent).
-template <int NI>
-struct WalkRecs {
-  int64_t s, d;
-  int in;
-};
-
-__device__ __forceinline__ void st_row_nt(char* row, uint32_t off, int n_bytes, u32x4 v) {
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc((void*)row, (short)0, n_bytes, kBufferRsrcWord3);
-  __builtin_amdgcn_raw_buffer_store_b128(v, rs, off, 0, kBufferNonTemporal);
-}
-
-template <int NI>
-__global__ __launch_bounds__(kCompactThreads) void k_inplace_walk(InplaceArgs a) {
-  static_assert(NI <= 64, "a tile's records fit one register per lane");
-  const int lane = threadIdx.x & 63;
-  // (the wavefront index made explicitly uniform, so that everything derived
-  // from it -- the walk's plane and slice, hence each row's buffer resource --
-  // lives in scalar registers)
-  const int64_t unit =
-      (int64_t)blockIdx.x * kCompactWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t per_seq = (int64_t)a.n_lk * a.n_slices;
-  const int b = (int)(unit / per_seq);
-  if (b >= a.B) return;
-  const int rem = (int)(unit - (int64_t)b * per_seq);
-  const int pl = rem / a.n_slices;
-  const int sl = rem - pl * a.n_slices;
-  const int h = a.info[2 * b];
-  const int nk = a.info[2 * b + 1];
-  if (h >= nk) return;
-  // this slice of a row: bytes [1024 sl, min(1024 sl + 1024, row_bytes))
-  char* base = a.pool + (int64_t)(pl >> 1) * a.s_layer + (int64_t)(pl & 1) * a.s_kv + 1024 * sl;
-  const int span = min(1024, a.row_bytes - 1024 * sl);
-  const uint32_t off = 16u * lane;
-  const int64_t* rec = a.offsets + 2 * (int64_t)b * a.K;
-  auto load_recs = [&](int j0, WalkRecs<NI>& r) {
-    const int t = j0 + lane;
-    r.in = lane < NI && t < nk;
-    const int tc = r.in ? t : h;
-    r.s = rec[2 * tc];
-    r.d = rec[2 * tc + 1];
-  };
-  // row i of a tile: its source (load) or destination (store) row base and
-  // the bytes it spans, 0 when absent -- read from lane i into scalars, so
-  // the row's buffer resource is wave-uniform
-  auto row_at = [&](const WalkRecs<NI>& r, int i, bool dst, int& n) -> char* {
-    const int64_t w = dst ? r.d : r.s;
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)(uint64_t)w, i);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)w >> 32), i);
-    const int64_t v = (int64_t)(((uint64_t)hi << 32) | lo);
-    const bool ok = __builtin_amdgcn_readlane(r.in, i) && v >= 0;
-    n = ok ? span : 0;
-    return ok ? base + v : base;
-  };
-  auto load_tile = [&](const WalkRecs<NI>& r, u32x4 (&v)[NI]) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      int n;
-      const char* q = row_at(r, i, false, n);
-      v[i] = ld_row_nt(q, off, n);
-    }
-  };
-  auto store_tile = [&](const WalkRecs<NI>& r, const u32x4 (&v)[NI]) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      int n;
-      char* q = row_at(r, i, true, n);
-      st_row_nt(q, off, n, v[i]);
-    }
-  };
-  WalkRecs<NI> r0, r1, r2;
-  load_recs(h, r0);
-  load_recs(h + NI, r1);
-  u32x4 va[NI], vb[NI];
-  load_tile(r0, va);  // (waits for r0 only)
-  for (int j0 = h;; j0 += 2 * NI) {
-    // tile at j0 in va (records r0), the next tile's records in r1
-    load_recs(j0 + 2 * NI, r2);
-    load_tile(r1, vb);
-    store_tile(r0, va);
-    if (j0 + NI >= nk) break;
-    load_recs(j0 + 3 * NI, r0);
-    load_tile(r2, va);
-    store_tile(r1, vb);
-    if (j0 + 2 * NI >= nk) break;
-    r1 = r0;
-    r0 = r2;
-  }
-}
-
-template <int LPR, int NI>
-hipError_t launch_move(const InplaceArgs& a, hipStream_t s) {
-  const int64_t units = (int64_t)a.B * a.n_lk * a.n_slices;
-  const int64_t blocks = (units + kCompactWaves - 1) / kCompactWaves;
-  hipLaunchKernelGGL((k_inplace_move<LPR, NI>), dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, a);
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -491,19 +406,13 @@ hipError_t launch_compact_inplace(const InplaceArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_inplace_check, dim3(a.B), dim3(kInplaceThreads), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  switch (a.lanes_per_row * 1000 + a.tile_ni) {
-    case 64016: {
-      const int64_t units = (int64_t)a.B * a.n_lk * a.n_slices;
-      const int64_t blocks = (units + kCompactWaves - 1) / kCompactWaves;
-      hipLaunchKernelGGL((k_inplace_walk<8>), dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, a);
-      return hipGetLastError();
-    }
-    case 16008: return launch_move<16, 8>(a, s);
-    case 16016: return launch_move<16, 16>(a, s);
-    case 4004: return launch_move<4, 4>(a, s);
-    case 4016: return launch_move<4, 16>(a, s);
-    default: return hipErrorInvalidValue;
-  }
+  const int64_t blocks = (int64_t)a.B * a.n_lk * a.n_slices;
+  const size_t lds = 4 * (kTileThreads / a.slice_vec * kTileLoads) * sizeof(i64x2);
+  if (kTileThreads % a.slice_vec == 0)
+    hipLaunchKernelGGL(k_inplace_tile<true>, dim3((unsigned)blocks), dim3(kTileThreads), lds, s, a);
+  else
+    hipLaunchKernelGGL(k_inplace_tile<false>, dim3((unsigned)blocks), dim3(kTileThreads), lds, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace epikv

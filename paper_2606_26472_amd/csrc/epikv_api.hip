@@ -552,27 +552,25 @@ InplaceArgs inplace_args(const epikv_cfg* c, const epikv_pool* pool, const int32
   a.page_size = c->page_size;
   a.row_bytes = row_bytes(c);
   a.n_lk = 2 * c->n_layers;
-  // A wavefront per (sequence, plane, column slice): the widest slice --
-  // 1 KiB or 256 B, that is 64 or 16 lanes per row -- that still gives
-  // enough independent walks to keep HBM busy (each walk has one tile in
-  // flight), with tiles of 16 and 32 rows.  Short of that (a few sequences)
-  // the walks stay 256 B wide and take 64-row tiles instead: narrower
-  // slices would give more walks, but 64-byte pieces of rows use HBM poorly
-  // (measured 2.7 TB/s at 64 B against 4.5 TB/s at 256 B for one
-  // sequence).  Rows narrower than 256 B use 64-byte slices.
+  // A workgroup per (sequence, plane, column slice), one to a compute unit.
+  // Of the slices that divide the row (8 to 256 columns) and have 256 bytes at
+  // least, the widest whose workgroups come out at nine tenths of whole rounds
+  // over the compute units; none does: the one that comes closest.  3 x 700
+  // rows of 2 KiB, 192 walks: 114 us whole, 110.5 us in slices of 512 bytes.
   const int row_vec = a.row_bytes / 16;
-  auto walks = [&](int lpr) { return (int64_t)a.B * a.n_lk * ((row_vec + lpr - 1) / lpr); };
-  if (row_vec >= 64 && walks(64) >= kInplaceUnitsWanted) {
-    a.lanes_per_row = 64;
-    a.tile_ni = 16;
-  } else if (row_vec >= 16) {
-    a.lanes_per_row = 16;
-    a.tile_ni = walks(16) >= kInplaceUnitsWanted ? 8 : 16;
-  } else {
-    a.lanes_per_row = 4;
-    a.tile_ni = walks(4) >= kInplaceUnitsWanted ? 4 : 16;
+  const int64_t cus = std::max(1, device_cus());
+  double best = -1.0;
+  for (int s = 1; s == 1 || row_vec / s >= 16; ++s) {
+    if (row_vec % s != 0) continue;
+    const int64_t blocks = (int64_t)a.B * a.n_lk * s;
+    const double full = (double)blocks / (double)((blocks + cus - 1) / cus * cus);
+    if (full > best) {
+      best = full;
+      a.n_slices = s;
+      a.slice_vec = row_vec / s;
+    }
+    if (full >= 0.9) break;
   }
-  a.n_slices = (row_vec + a.lanes_per_row - 1) / a.lanes_per_row;
   return a;
 }
 

@@ -223,9 +223,8 @@ struct InplaceArgs {
   int32_t* remap_ws;                       // workspace [B][4][n_pg]
   int32_t n_pg;
   int32_t B, K, page_size, row_bytes, n_lk;
-  int32_t lanes_per_row;                   // 64, 16 or 4 lanes share one row of a plane
-  int32_t n_slices;                        // ceil(row_bytes / 16 / lanes_per_row)
-  int32_t tile_ni;                         // row loads per lane and tile
+  int32_t slice_vec;                       // 16-byte columns of a walk's slice
+  int32_t n_slices;                        // slices of a row
 };
 
 struct FillArgs {
@@ -396,9 +395,8 @@ constexpr uint32_t kSelMarkLo = 0x9E3779B9u;              // "this scratch is cl
 constexpr uint32_t kSelMarkHi = 0x7F4A7C15u;
 constexpr int kSelSeqWords = kSelHeadWords + 3 * 2048;    // per-sequence scratch words
 constexpr int kSelMaxGrid = 256;  // workgroups of a multi-workgroup selection, at most
-constexpr int kCompactThreads = 256;      // resolve kernel; in-place move workgroups
+constexpr int kCompactThreads = 256;      // resolve kernel
 constexpr int64_t kCompactGridX = 1 << 24;  // gather workgroups per grid row
-constexpr int kCompactWaves = kCompactThreads / 64;  // walks per in-place move workgroup
 constexpr int kLagWgWanted = 512;        // split a plane's rows until this many workgroups
 constexpr int kLagPtCache = 1024;        // page-table entries a KV-scorer workgroup keeps in LDS
 // Bytes of a call's rows from which on its first chunks' ranges are found by
@@ -454,6 +452,5 @@ __host__ __device__ inline int lagkv_range_floats(int H, int d, bool big) {
 constexpr int kRedRowWords = 64 * 2 + 8 * 4;
 size_t lagkv_lds_bytes(int H, int d, bool lag, bool big);
 constexpr int kInplaceThreads = 1024;    // per-sequence check + score move
-constexpr int kInplaceUnitsWanted = 2048;  // narrow the column slices below this
 
 }  // namespace epikv
