@@ -259,21 +259,32 @@ __device__ __forceinline__ float smooth_at(const float* x, int base, int lo, int
   if (mode == EPIKV_SMOOTH_RAW) return xv;
   float s = 0.f;
   if (!__any(j - lo != 63)) {
-    // Full windows of 64 samples: read once into registers, all reads ahead
-    // of the additions (as two loops over LDS below, 0.6 us longer in the
-    // smoothing of a step's chunk: smoothing + resolve 6.3 -> 5.7 us).
-    float v[64];
+    // Full windows of 64 samples: 32 reads ahead of their additions, against
+    // the loops below with a remainder: 64 x 1000 tokens 16.8 -> 14.8 us, one
+    // 65,536-token chunk 16.4 -> 14.7 us, a step's smoothing + resolve 6.3 ->
+    // 5.8 us.  (All 64 kept in registers for both passes left one workgroup
+    // per compute unit: 22.0 us for the first.)
+    const float* w = x + (lo - base);
+    float v[32];
+#pragma unroll 1
+    for (int h = 0; h < 64; h += 32) {
 #pragma unroll
-    for (int k = 0; k < 64; ++k) v[k] = x[lo - base + k];
+      for (int k = 0; k < 32; ++k) v[k] = w[h + k];
 #pragma unroll
-    for (int k = 0; k < 64; ++k) s += v[k];
+      for (int k = 0; k < 32; ++k) s += v[k];
+    }
     const float mu = s / n;
     if (mode == EPIKV_SMOOTH_MEAN) return mu;
     float q = 0.f;
+#pragma unroll 1
+    for (int h = 0; h < 64; h += 32) {
 #pragma unroll
-    for (int k = 0; k < 64; ++k) {
-      const float dlt = v[k] - mu;
-      q = fmaf(dlt, dlt, q);
+      for (int k = 0; k < 32; ++k) v[k] = w[h + k];
+#pragma unroll
+      for (int k = 0; k < 32; ++k) {
+        const float dlt = v[k] - mu;
+        q = fmaf(dlt, dlt, q);
+      }
     }
     return (xv - mu) / (sqrtf(q / n) + eps);
   }
