@@ -48,13 +48,13 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact_resolve(CompactArgs
   compact_impl::resolve_slot(a, blockIdx.y, j, INT64_MAX);
 }
 
-// Rows of whole KiB (1024, 2048, ... bytes).  Workgroup x (linear over
-// blockIdx.z, blockIdx.x): record x / units, its columns [64 u, 64 u + 64)
-// with u = x % units, in plane blockIdx.y.  The record is wave-uniform (a
+// Rows of whole KiB (1024, 2048, ... bytes).  Workgroup x (linear_block):
+// record x / units, its columns [64 u, 64 u + 64) with u = x % units, in
+// plane blockIdx.y.  The record is wave-uniform (a
 // scalar load).
 __global__ __launch_bounds__(64) void k_compact(CompactArgs a, int64_t total) {
   const int lane = threadIdx.x;
-  const int64_t x = (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
+  const int64_t x = linear_block();
   if (x >= total) return;
   const int64_t r = x / a.units;
   const int u = (int)(x - r * a.units);
@@ -82,7 +82,7 @@ template <int RPW>
 __global__ __launch_bounds__(64) void k_compact_rows(CompactArgs a, int64_t total) {
   constexpr int LPR = 64 / RPW;
   const int lane = threadIdx.x;
-  const int64_t r0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * RPW;
+  const int64_t r0 = linear_block() * RPW;
   const int sub = lane / LPR;
   int64_t s0 = -1, d0 = -1;
 #pragma unroll
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64) void k_compact_rows(CompactArgs a, int64_t tota
 // 1039 us (8 x 4096 rows, 64 planes; 6.2-6.3 TB/s).
 __global__ __launch_bounds__(64) void k_compact_vecs(CompactArgs a, int64_t total) {
   const int row_vec = a.row_bytes >> 4;
-  const int64_t v0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * 64;
+  const int64_t v0 = linear_block() * 64;
   const int64_t q = v0 / row_vec;  // (wave-uniform)
   const int t = (int)(v0 - q * row_vec) + (int)threadIdx.x;
   const int64_t r = q + t / row_vec;
@@ -126,12 +126,8 @@ __global__ __launch_bounds__(64) void k_compact_vecs(CompactArgs a, int64_t tota
   st_stream(db + c * 16, ld_stream(sb + c * 16));
 }
 
-// One workgroup per `n` units in order, the linear index split as
-// blockIdx.z * gridDim.x + blockIdx.x, and one grid row per plane.
-dim3 gather_grid(int64_t n, int planes) {
-  const int64_t gx = n < kCompactGridX ? n : kCompactGridX;
-  return dim3((unsigned)gx, planes, (unsigned)((n + gx - 1) / gx));
-}
+// `n` workgroups in order for each plane.
+dim3 gather_grid(int64_t n, int planes) { return linear_grid(n, 64, planes); }
 
 }  // namespace
 

@@ -329,8 +329,10 @@ __global__ __launch_bounds__(kTileThreads) void k_inplace_tile(InplaceArgs a) {
   const int rpi = kTileThreads / a.slice_vec;  // rows per load
   const int T = rpi * kTileLoads;              // (at most kTileThreads)
   const int per_seq = a.n_lk * a.n_slices;
-  const int b = blockIdx.x / per_seq;
-  const int rem = blockIdx.x - b * per_seq;
+  const uint32_t walk = (uint32_t)linear_block();  // (2^27 planes of 4 slices at most)
+  const int b = walk / per_seq;
+  if (b >= a.B) return;
+  const int rem = walk - b * per_seq;
   const int pl = rem / a.n_slices;
   const int sl = rem - pl * a.n_slices;
   const int h = a.info[2 * b];
@@ -406,12 +408,12 @@ hipError_t launch_compact_inplace(const InplaceArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_inplace_check, dim3(a.B), dim3(kInplaceThreads), 0, s, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t blocks = (int64_t)a.B * a.n_lk * a.n_slices;
+  const dim3 grid = linear_grid((int64_t)a.B * a.n_lk * a.n_slices, kTileThreads);
   const size_t lds = 4 * (kTileThreads / a.slice_vec * kTileLoads) * sizeof(i64x2);
   if (kTileThreads % a.slice_vec == 0)
-    hipLaunchKernelGGL(k_inplace_tile<true>, dim3((unsigned)blocks), dim3(kTileThreads), lds, s, a);
+    hipLaunchKernelGGL(k_inplace_tile<true>, grid, dim3(kTileThreads), lds, s, a);
   else
-    hipLaunchKernelGGL(k_inplace_tile<false>, dim3((unsigned)blocks), dim3(kTileThreads), lds, s, a);
+    hipLaunchKernelGGL(k_inplace_tile<false>, grid, dim3(kTileThreads), lds, s, a);
   return hipGetLastError();
 }
 

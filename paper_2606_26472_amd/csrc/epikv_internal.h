@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "epikv.h"
 
 namespace epikv {
@@ -351,6 +353,16 @@ __device__ __forceinline__ float band_combine(const float (*vals)[TILE], int t, 
 // ---------------------------------------------------------------------------
 // Compute units of the current device (0 if the query fails).
 int device_cus();
+// Workgroups 0, 1, ... n - 1 in order, split over x and z: a launch with 2^32
+// threads or more in one dimension is not refused, it runs a part of its
+// workgroups.  The last z may hold workgroups past n - 1, which have to leave.
+inline dim3 linear_grid(int64_t n, int threads, int y = 1) {
+  const int64_t gx = std::min<int64_t>(n, (1 << 30) / threads);
+  return dim3((unsigned)gx, (unsigned)y, (unsigned)((n + gx - 1) / gx));
+}
+__device__ __forceinline__ int64_t linear_block() {
+  return (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
+}
 hipError_t launch_score_hs(const ScoreHsArgs& a, hipStream_t s);
 hipError_t launch_score_tokens(const ScoreTokArgs& a, hipStream_t s);
 hipError_t launch_score_lagkv(const ScoreLagArgs& a, hipStream_t s);
@@ -407,7 +419,6 @@ constexpr uint32_t kSelMarkHi = 0x7F4A7C15u;
 constexpr int kSelSeqWords = kSelHeadWords + 3 * 2048;    // per-sequence scratch words
 constexpr int kSelMaxGrid = 256;  // workgroups of a multi-workgroup selection, at most
 constexpr int kCompactThreads = 256;      // resolve kernel
-constexpr int64_t kCompactGridX = 1 << 24;  // gather workgroups per grid row
 constexpr int kLagWgWanted = 512;        // split a plane's rows until this many workgroups
 constexpr int kLagPtCache = 1024;        // page-table entries a KV-scorer workgroup keeps in LDS
 // Bytes of a call's rows from which on its first chunks' ranges are found by
