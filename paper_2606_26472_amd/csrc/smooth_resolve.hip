@@ -20,16 +20,19 @@ template <bool EMA>
 __global__ __launch_bounds__(kZscoreThreads) void k_smooth_resolve(ZscoreArgs a, CompactArgs ca,
                                                                    int per, int smooth,
                                                                    int blocks_seq) {
-  if ((int)blockIdx.x >= smooth) {
-    const int x = blockIdx.x - smooth;
+  // (31 bits: 16 bytes of workspace for each slot, 64 tokens for each tile)
+  const int blk = (int)linear_block();
+  if (blk >= smooth) {
+    const int x = blk - smooth;
     const int b = x / blocks_seq;
+    if (b >= a.B) return;
     const int j = (x - b * blocks_seq) * kZscoreThreads + threadIdx.x;
     if (j < ca.n_pg * ca.page_size) compact_impl::resolve_slot(ca, b, j, a.n_cached[b] - a.C);
     return;
   }
   const int tiles_seq = smooth / a.B;
-  const int b = blockIdx.x / tiles_seq;
-  const int t = blockIdx.x - b * tiles_seq;
+  const int b = blk / tiles_seq;
+  const int t = blk - b * tiles_seq;
   // Where token c's score goes besides its own place: it is the (C - c)-th
   // from the end of the kept positions, too.
   auto copy_of = [&](int c) -> float* {
@@ -63,7 +66,7 @@ hipError_t launch_smooth_resolve(const ZscoreArgs& a, const CompactArgs& ca, hip
   const int per = ema ? zscore_impl::ema_per(a) : 1;
   const int smooth = (zscore_impl::tiles_of(a) + per - 1) / per * a.B;
   const int blocks_seq = (ca.n_pg * ca.page_size + kZscoreThreads - 1) / kZscoreThreads;
-  const dim3 grid((unsigned)smooth + (unsigned)blocks_seq * (unsigned)a.B);
+  const dim3 grid = linear_grid(smooth + (int64_t)blocks_seq * a.B, kZscoreThreads);
   if (ema)
     hipLaunchKernelGGL(k_smooth_resolve<true>, grid, dim3(kZscoreThreads), 0, s, a, ca, per, smooth,
                        blocks_seq);

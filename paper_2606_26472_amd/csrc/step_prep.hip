@@ -30,11 +30,11 @@ struct PrepArgs {
 enum { kWindow, kWindowKv, kEma };
 
 template <int MODE>
-__device__ __forceinline__ void smooth(const PrepArgs& a) {
+__device__ __forceinline__ void smooth(const PrepArgs& a, int blk) {
   const ZscoreArgs& z = a.zs;
   const int tiles_seq = a.smooth / z.B;
-  const int b = blockIdx.x / tiles_seq;
-  const int t = blockIdx.x - b * tiles_seq;
+  const int b = blk / tiles_seq;
+  const int t = blk - b * tiles_seq;
   auto put = [&](int b, int c, int N, float s) { zscore_impl::put_score(z, b, c, N, s); };
   if (MODE == kEma) {
     zscore_impl::ema_tiles(z, t, a.per, b, put);
@@ -66,9 +66,9 @@ __device__ __forceinline__ void smooth(const PrepArgs& a) {
 
 template <int MODE>
 __global__ __launch_bounds__(kPrepThreads) void k_step_prep(PrepArgs a) {
-  int x = blockIdx.x;
+  int x = (int)linear_block();  // (31 bits: 64 tokens, 1024 words or ranges each)
   if (x < a.smooth) {
-    smooth<MODE>(a);
+    smooth<MODE>(a, x);
     return;
   }
   x -= a.smooth;
@@ -79,15 +79,17 @@ __global__ __launch_bounds__(kPrepThreads) void k_step_prep(PrepArgs a) {
   }
   x -= a.clear;
   if (MODE == kWindowKv) {
-    const int b = x / a.range_seq;
+    const int b = a.range_seq > 0 ? x / a.range_seq : a.red.B;
+    if (b >= a.red.B) return;
     const int i = (x - b * a.range_seq) * kPrepThreads + threadIdx.x;
     if (i < a.red.n_chan) lag_reduce_impl::chunk_range(a.red, b, i);
   }
 }
 
 template <int MODE>
-hipError_t launch(const PrepArgs& a, unsigned blocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_step_prep<MODE>, dim3(blocks), dim3(kPrepThreads), 0, s, a);
+hipError_t launch(const PrepArgs& a, int64_t blocks, hipStream_t s) {
+  hipLaunchKernelGGL(k_step_prep<MODE>, linear_grid(blocks, kPrepThreads), dim3(kPrepThreads), 0, s,
+                     a);
   return hipGetLastError();
 }
 
@@ -112,8 +114,8 @@ hipError_t launch_step_prep(const ZscoreArgs& zs, const LagReduceArgs* red, cons
       a.range_seq = (red->n_chan + kPrepThreads - 1) / kPrepThreads;
     blocks += (int64_t)a.range_seq * red->B;
   }
-  if (zs.mode == EPIKV_SMOOTH_EMA) return launch<kEma>(a, (unsigned)blocks, s);
-  return red ? launch<kWindowKv>(a, (unsigned)blocks, s) : launch<kWindow>(a, (unsigned)blocks, s);
+  if (zs.mode == EPIKV_SMOOTH_EMA) return launch<kEma>(a, blocks, s);
+  return red ? launch<kWindowKv>(a, blocks, s) : launch<kWindow>(a, blocks, s);
 }
 
 }  // namespace epikv
