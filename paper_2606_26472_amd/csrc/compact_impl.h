@@ -36,7 +36,8 @@ __device__ __forceinline__ uint32_t block_exclusive_sum(uint32_t v, uint32_t* ws
 
 // The order stage, on one workgroup of kOrderThreads threads.  n_keep(b):
 // rows kept of sequence b, or negative.  Any value of it gives ranks that are
-// a permutation, so a wrong one would cost speed only.
+// a permutation, so a wrong one would cost speed only -- but it has to be the
+// same each time: it is asked once for the counts and again for the ranks.
 template <typename NKeep>
 __device__ __forceinline__ void order_pages(const CompactArgs& a, NKeep n_keep) {
   __shared__ uint32_t bits[kOrderWords];

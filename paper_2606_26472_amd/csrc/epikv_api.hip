@@ -585,6 +585,22 @@ int check_remap_table(const epikv_cfg* c, const int32_t* pt, int64_t ld_pt, cons
   return EPIKV_OK;
 }
 
+// The order stage may run beside the selection while the selection writes
+// nothing that it reads more than once (a caller may pass the counts that the
+// step updates as both n_cached and n_keep): it needs the same counts in all
+// of its passes, or ranks collide and records stay unwritten.
+bool order_beside(const epikv_cfg* c, const epikv_step_io* io) {
+  const size_t B = (size_t)c->batch;
+  const void* in[] = {io->n_cached, io->n_prefix, io->dst_pt};
+  const size_t in_n[] = {4 * B, 4 * B, 4 * B * (size_t)io->ld_dst_pt};
+  const void* out[] = {io->keep_idx, io->n_keep, io->seq_status};
+  const size_t out_n[] = {4 * B * (size_t)c->budget, 4 * B, 4 * B};
+  for (int i = 0; i < 3; ++i)
+    for (int o = 0; o < 3; ++o)
+      if (overlap(in[i], in_n[i], out[o], out_n[o])) return false;
+  return true;
+}
+
 InplaceArgs remap_args(InplaceArgs a, int32_t* pt) {
   a.remap = 1;
   a.pt_out = pt;
@@ -874,6 +890,7 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
     ca = compact_args(cfg, &io->src, io->src_pt, io->ld_src_pt, &io->dst, io->dst_pt,
                       io->ld_dst_pt, io->keep_idx, io->n_keep, src_scores, io->dst_scores,
                       io->src_pos, io->dst_pos, io->ld_s, io->seq_status, ws_offsets);
+  const CompactArgs* beside = !io->in_place && order_beside(cfg, io) ? &ca : nullptr;
   bool selected = false;  // the select stage is on the stream
   if (scoring && cfg->signal == EPIKV_SIGNAL_HS) {
     const ScoreHsArgs hs =
@@ -883,10 +900,11 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
       // older, frozen scores, so it runs beside the scoring (and the
       // ordering of the destination pages), then the chunk's scores are
       // smoothed and written (beside the resolve stage).
-      st = launched(launch_select_score(sel, hs, io->in_place ? nullptr : &ca, stream));
+      st = launched(launch_select_score(sel, hs, beside, stream));
       if (st) return st;
       if (!io->in_place) {
-        st = launched(launch_smooth_resolve(zs, ca, stream));
+        if (!beside) st = launched(launch_compact_order(ca, stream));
+        if (!st) st = launched(launch_smooth_resolve(zs, ca, stream));
         return st ? st : launched(launch_compact_gather(ca, stream));
       }
       st = launched(launch_zscore(zs, stream));
@@ -913,7 +931,7 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
       if (st) return st;
     }
     // (the prep launch has cleared the selection's scratch)
-    st = launched(launch_select_groups(sel, ws_select, scoring, io->in_place ? nullptr : &ca, stream));
+    st = launched(launch_select_groups(sel, ws_select, scoring, beside, stream));
     if (st) return st;
   }
   if (io->in_place) {
@@ -923,6 +941,7 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
     if (io->in_place == EPIKV_COMPACT_REMAP) a = remap_args(a, const_cast<int32_t*>(io->src_pt));
     return launched(launch_compact_inplace(a, stream));
   }
-  st = launched(launch_compact_resolve(ca, stream));
+  if (!beside) st = launched(launch_compact_order(ca, stream));
+  if (!st) st = launched(launch_compact_resolve(ca, stream));
   return st ? st : launched(launch_compact_gather(ca, stream));
 }

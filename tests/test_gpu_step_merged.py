@@ -64,7 +64,18 @@ def test_unfused_step_equals_its_stages(E, C, D, lengths):
     _compare(E, "z", C, 16, "scattered", False, lengths, 600, D=D)
 
 
-def _compare(E, smoothing, C, page, order, bad, lengths, K, signal="hs", window=64, H=1, D=64):
+@pytest.mark.parametrize("signal,C,lengths,K", [
+    ("hs", 0, [1500, 700, 10, 1300], 600),          # nothing to score
+    ("hs", 120, [1500, 700, 120, 1300], 100),       # a chunk longer than the budget
+    ("lagkv", 120, [300, 250, 120, 299], 100)])     # the same; the selection is not split
+def test_counts_updated_in_place(E, signal, C, lengths, K):
+    """One buffer as n_cached and n_keep: the page order, which needs the
+    counts, must not run beside the selection that rewrites them."""
+    _compare(E, "mean", C, 16, "scattered", False, lengths, K, signal, counts_in_place=True)
+
+
+def _compare(E, smoothing, C, page, order, bad, lengths, K, signal="hs", window=64, H=1, D=64,
+             counts_in_place=False):
     import torch
     print(f"merged step {signal} {smoothing} C={C} page={page} {order} bad={bad}", flush=True)
     g = synth.rng(2100 + C + page)
@@ -122,7 +133,10 @@ def _compare(E, smoothing, C, page, order, bad, lengths, K, signal="hs", window=
     a, s = outputs(), outputs()
     n = E.workspace_bytes(cfg, C)
     ws = torch.full((n,), 0x7F, dtype=torch.uint8, device="cuda")
-    io = E.make_step_io(C, hidden, D, C * D, n_cached, n_prefix, src, spt, src_pt.shape[1],
+    if counts_in_place:
+        a["nk"].copy_(n_cached)
+    io = E.make_step_io(C, hidden, D, C * D, a["nk"] if counts_in_place else n_cached, n_prefix,
+                        src, spt, src_pt.shape[1],
                         E.pool_of(a["dst"].view(L, 2, n_dst, page, H, d)), dpt, dst_pt.shape[1],
                         a["scores"], ld_s, st_in, a["st_out"], a["keep"], a["nk"], a["status"],
                         ws, n, dst_scores=a["dsc"], src_pos=pos, dst_pos=a["dpos"])
