@@ -293,31 +293,29 @@ __global__ __launch_bounds__(kInplaceThreads) void k_inplace_check(InplaceArgs a
   }
 }
 
-// The move: one 1024-thread workgroup per walk,
-// a thread per 16-byte column of a row of the slice, tiles of T rows (eight
-// loads per thread: 64 rows of 2 KiB), software pipelined: tile k + 1's loads
-// are issued before tile k's stores.  This keeps the ordering argument: a
-// tile's stores follow a barrier behind which all of its loads have returned,
-// and tile k + 1 reads positions at or past its own slots, which lie past every
-// slot that tile k (or an earlier one) writes.  One barrier per tile: the
-// records of four tiles are in LDS, written two tiles ahead.
+// The move: one 1024-thread workgroup per walk, a thread per 16-byte column of
+// a row of the slice (inplace_slices), tiles of T rows (eight loads per thread:
+// 64 rows of 2 KiB), software pipelined: tile k + 1's loads are issued before
+// tile k's stores.  This keeps the ordering argument: a tile's stores follow a
+// barrier behind which all of its loads have returned, and tile k + 1 reads
+// positions at or past its own slots, which lie past every slot that tile k (or
+// an earlier one) writes.  One barrier per tile: the records of four tiles are
+// in LDS, written two tiles ahead.
 //
 // Bound by HBM as a walk sees it.  Every load and every store of a full tile
 // is issued on every path, so that a wait is exactly for the tile it needs and
 // never for the stores in between (only the last tile's stores are conditional,
 // and without ALL, where the slice's columns do not divide 1024, those of the
-// threads left over).  A workgroup's tile is one run of 128 KiB where pages are; wavefronts
-// that walked 1 KiB slices by themselves, 2048 of them with 8 rows each, put
-// as many bytes in flight but spread them over 2048 places.
-// Measured, K + 128 -> K and rows of 2 KiB in 64 planes, wavefronts -> this:
-// 16 x 4096 rows 3346 -> 3334 us (5.1 TB/s), 1 x 2000 119 -> 104 us, 1 x 300
-// 21.1 -> 17.0 us, 3 x 700 113.7 -> 110.5 us; rows of 256 bytes (16 x 4096)
-// 438 -> 428 us; of 1536, 768 and 1280 bytes (1 x 2000, 2 x 1000, 4 x 600 rows;
-// their last slices of a row were part empty) 111.5 -> 81.3, 58.2 -> 38.3 and
-// 94.5 -> 81.4 us.  Large batches stay at 5.1 TB/s however they are cut: a
-// plain copy with its destination 256 KiB ahead of its source in the same
-// buffer runs at 4.7 to 5.9 TB/s with the distance between the two, and here
-// that distance grows along the walk.
+// threads left over).
+// Measured, K + 128 -> K and rows of 2 KiB in 64 planes, a wavefront per walk of
+// 1 KiB or 256-byte slices -> this, in turn on the same buffers: 16 x 4096 rows
+// 3352 -> 3368 us (5.1 TB/s), 1 x 2000 120 -> 106 us, 1 x 300 22.3 -> 18.2 us,
+// 3 x 700 115.5 -> 111.6 us; rows of 256 bytes (16 x 4096) 441 -> 434 us; of
+// 1536, 768 and 1280 bytes (1 x 2000, 2 x 1000, 4 x 600 rows) 111 -> 82, 57 ->
+// 37 and 95 -> 81 us.  Large batches stay at 5.1 TB/s with either: a plain copy
+// with its destination 256 KiB ahead of its source in the same buffer runs at
+// 4.7 to 5.9 TB/s with the distance between the two, and here that distance
+// grows along the walk.
 constexpr int kTileThreads = 1024;
 constexpr int kTileLoads = 8;
 typedef int64_t i64x2 __attribute__((ext_vector_type(2)));

@@ -523,6 +523,42 @@ int check_compact_inplace(const epikv_cfg* c, const epikv_pool* pool, const int3
   return EPIKV_OK;
 }
 
+// The in-place move's column slices: a workgroup per (plane of a sequence,
+// slice), one to a compute unit.  A slice is a divisor of the row in whole
+// 128-byte lines (8 columns): lines shared by two slices cost up to half of the
+// rate (3 x 2048 rows of 1152 bytes 298 us in quarters, 186 us whole; of 1280
+// bytes 247 us in quarters, 212 us whole).  In this order:
+// - the widest slice whose workgroups run in one round and fill six tenths
+//   of the units: 3 x 300 rows of 1 KiB 25.1 us whole, 27.9 us in quarters that
+//   fill three rounds;
+// - 512 bytes (2 KiB of wider rows) if they come out at nine tenths of whole
+//   rounds: 8 x 2048 rows of 2 KiB 884 us so, 910 us whole; of 4 KiB 1626 us in
+//   halves, 1700 us whole;
+// - the widest that does, or else the one that comes closest: 5 x 2048 rows of
+//   1408 bytes 381 us in eleven slices, 430 us whole.
+void inplace_slices(int64_t planes, int row_vec, int64_t cus, int32_t* n, int32_t* vec) {
+  auto take = [&](int s) {
+    *n = s;
+    *vec = row_vec / s;
+  };
+  auto fits = [&](int s) { return row_vec % s == 0 && row_vec / s % 8 == 0; };
+  auto fill = [&](int s) {  // of whole rounds
+    const int64_t blocks = planes * s;
+    return (double)blocks / (double)((blocks + cus - 1) / cus * cus);
+  };
+  for (int s = 1; planes * s <= cus && s <= row_vec; ++s)
+    if (fits(s) && fill(s) >= 0.6) return take(s);
+  const int cols = row_vec > 128 ? 128 : 32;
+  if (planes > cus && row_vec % cols == 0 && fill(row_vec / cols) >= 0.9)
+    return take(row_vec / cols);
+  double best = -1.0;
+  for (int s = 1; s <= row_vec && best < 0.9; ++s)
+    if (fits(s) && fill(s) > best) {
+      best = fill(s);
+      take(s);
+    }
+}
+
 InplaceArgs inplace_args(const epikv_cfg* c, const epikv_pool* pool, const int32_t* pt,
                          int64_t ld_pt, const int32_t* keep_idx, const int32_t* n_keep,
                          float* scores, int32_t* pos, int64_t ld_s, int32_t* seq_status,
@@ -552,25 +588,8 @@ InplaceArgs inplace_args(const epikv_cfg* c, const epikv_pool* pool, const int32
   a.page_size = c->page_size;
   a.row_bytes = row_bytes(c);
   a.n_lk = 2 * c->n_layers;
-  // A workgroup per (sequence, plane, column slice), one to a compute unit.
-  // Of the slices that divide the row (8 to 256 columns) and have 256 bytes at
-  // least, the widest whose workgroups come out at nine tenths of whole rounds
-  // over the compute units; none does: the one that comes closest.  3 x 700
-  // rows of 2 KiB, 192 walks: 114 us whole, 110.5 us in slices of 512 bytes.
-  const int row_vec = a.row_bytes / 16;
-  const int64_t cus = std::max(1, device_cus());
-  double best = -1.0;
-  for (int s = 1; s == 1 || row_vec / s >= 16; ++s) {
-    if (row_vec % s != 0) continue;
-    const int64_t blocks = (int64_t)a.B * a.n_lk * s;
-    const double full = (double)blocks / (double)((blocks + cus - 1) / cus * cus);
-    if (full > best) {
-      best = full;
-      a.n_slices = s;
-      a.slice_vec = row_vec / s;
-    }
-    if (full >= 0.9) break;
-  }
+  inplace_slices((int64_t)a.B * a.n_lk, a.row_bytes / 16, std::max(1, device_cus()), &a.n_slices,
+                 &a.slice_vec);
   return a;
 }
 
