@@ -20,19 +20,25 @@ constexpr int kWaves = kZscoreThreads / 64;
 constexpr int kSlice = EPIKV_MAX_WINDOW - 1 + kZscoreTile;
 constexpr int kRing = (EPIKV_MAX_WINDOW - 1 + 63) / 64;  // carried samples per lane
 
+// How a wavefront walks the chunk's rows.
+enum { kOneToken, kRowByRow, kPipelined };
+
 // Bound by latency: at one token per call a workgroup reads 15 rows of 8 KiB
 // and their predecessors, and every load is issued before the first wait, none
 // behind another's value (a fresh stream's predecessor is loaded and dropped,
-// as its count comes with the rows).  Of more tokens R - 1 rows are in flight
-// while one is compared with the row before it, which takes R buffers in turn;
-// the waits are exact because every load is issued, past the chunk an empty
-// one.  A wavefront works on its own rows alone until the bands meet.
-// One token of 1 and 32 sequences (15 rows of 4096): launch 10.3 -> 6.7 us and
-// 12.0 -> 8.7 us, against a chain of count, carried samples, rows and window
-// sums that waited on one another; 8 tokens of 16 sequences 28.0 -> 26.2 us.
-template <int VPW, bool ONE>
+// as its count comes with the rows).  A wavefront works on its own rows alone
+// until the bands meet.  Against a chain of count, carried samples, rows and
+// window sums that waited on one another, one token of 1 and 32 sequences (15
+// rows of 4096): launch 10.3 -> 6.7 us and 12.0 -> 8.7 us.
+// Of more tokens (launch_score_tokens), kRowByRow compares each row with the
+// one before it in registers and then loads the next; kPipelined keeps R - 1
+// rows in flight, in R buffers that take turns: the waits are exact because
+// every load is issued, past the chunk an empty one.
+// (The widest pipeline has 12 registers in scratch: values of the smoothing,
+// which the loop over the rows does not touch.)
+template <int VPW, int WALK>
 __global__ __launch_bounds__(kZscoreThreads) void k_score_tokens(ScoreTokArgs a) {
-  constexpr int R = ONE ? 2 : VPW == 8 ? 3 : VPW == 4 ? 5 : 8;
+  constexpr int R = WALK != kPipelined ? 2 : VPW >= 4 ? 3 : 4;
   __shared__ float xs[kWaves][kSlice];
   __shared__ float vals[EPIKV_MAX_BAND][kZscoreTile];
   const int tid = threadIdx.x;
@@ -79,28 +85,49 @@ __global__ __launch_bounds__(kZscoreThreads) void k_score_tokens(ScoreTokArgs a)
 #pragma unroll
       for (int i = 0; i < VPW; ++i) {
         acc = sqdiff8(cur[i], prev[i], acc);
-        if (!ONE) __builtin_amdgcn_sched_barrier(0);  // (few unpacked values at a time)
+        // (few unpacked values at a time)
+        if (WALK == kPipelined) __builtin_amdgcn_sched_barrier(0);
       }
       const float g2 = wave_sum(acc);
       if (lane == 0) x[wm1 + c] = (fresh && c == 0) ? 0.f : sqrtf(g2);
-      if (c == a.C - 1) {
-        // the chunk's last row is the next call's predecessor
-        const __amdgpu_buffer_rsrc_t hout = __builtin_amdgcn_make_buffer_rsrc(
-            a.h_prev_out + row * a.D, (short)0, 2 * a.D, kBufferRsrcWord3);
-#pragma unroll
-        for (int i = 0; i < VPW; ++i)
-          __builtin_amdgcn_raw_buffer_store_b128(cur[i], hout, 16 * (lane + 64 * i), 0, 0);
-      }
     };
-    if (ONE) {
+    // the chunk's last row is the next call's predecessor
+    auto carry_row = [&](const u32x4 (&v)[VPW]) {
+      const __amdgpu_buffer_rsrc_t hout = __builtin_amdgcn_make_buffer_rsrc(
+          a.h_prev_out + row * a.D, (short)0, 2 * a.D, kBufferRsrcWord3);
+#pragma unroll
+      for (int i = 0; i < VPW; ++i)
+        __builtin_amdgcn_raw_buffer_store_b128(v[i], hout, 16 * (lane + 64 * i), 0, 0);
+    };
+    if (WALK == kOneToken) {
       change(0, buf[0], buf[1]);
+      carry_row(buf[1]);
+    } else if (WALK == kRowByRow) {
+#pragma unroll 1
+      for (int c = 0; c < a.C; ++c) {
+        if (c > 0) {
+#pragma unroll
+          for (int i = 0; i < VPW; ++i) {
+            const int v = lane + 64 * i;
+            buf[1][i] = v < a.D / 8 ? ld_stream(rows + (int64_t)c * a.ld_tok + v * 8)
+                                    : u32x4{0u, 0u, 0u, 0u};
+          }
+        }
+        change(c, buf[0], buf[1]);
+#pragma unroll
+        for (int i = 0; i < VPW; ++i) buf[0][i] = buf[1][i];
+      }
+      carry_row(buf[0]);
     } else {
 #pragma unroll 1
       for (int cb = 0; cb < a.C; cb += R) {
 #pragma unroll
         for (int u = 0; u < R; ++u) {
           const int c = cb + u;
-          if (c < a.C) change(c, buf[u], buf[(u + 1) % R]);
+          if (c < a.C) {
+            change(c, buf[u], buf[(u + 1) % R]);
+            if (c == a.C - 1) carry_row(buf[(u + 1) % R]);
+          }
           // (the row is unpacked again as the next one's predecessor: its
           // 8 * VPW values kept instead would spill)
 #pragma unroll
@@ -145,13 +172,26 @@ __global__ __launch_bounds__(kZscoreThreads) void k_score_tokens(ScoreTokArgs a)
   if (tid == 0) a.n_tok_out[b] = n_tok + a.C;
 }
 
+template <int VPW, int WALK>
+hipError_t launch_walk(const ScoreTokArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((k_score_tokens<VPW, WALK>), dim3(a.B), dim3(kZscoreThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+// Short chunks go row by row: what a pipeline of empty loads costs at its end
+// is more than it hides (4 tokens of 16 sequences, rows of 2048: 9.8 us against
+// 10.7; 8 tokens 15.2 against 15.4).  So do rows of more than 2048 with many
+// sequences: 16 KiB in flight for each of 480 wavefronts on an XCD's compute
+// units are more than its L2 holds (16 tokens of 256 sequences 97 us against
+// 110, of 64 sequences 48.5 against 49.5; 64 tokens of 64 sequences 170 against
+// 162).  Narrower rows gain at any number (16 tokens of 256 sequences, rows of
+// 2048 and 1024: 50.2 -> 49.0 us and 26.7 -> 24.2 us against two rows at a time
+// with their loads behind one another).
 template <int VPW>
 hipError_t launch(const ScoreTokArgs& a, hipStream_t s) {
-  if (a.C == 1)
-    hipLaunchKernelGGL((k_score_tokens<VPW, true>), dim3(a.B), dim3(kZscoreThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_score_tokens<VPW, false>), dim3(a.B), dim3(kZscoreThreads), 0, s, a);
-  return hipGetLastError();
+  if (a.C == 1) return launch_walk<VPW, kOneToken>(a, s);
+  if (a.C <= 8 || (VPW == 8 && a.B > 64)) return launch_walk<VPW, kRowByRow>(a, s);
+  return launch_walk<VPW, kPipelined>(a, s);
 }
 
 }  // namespace
