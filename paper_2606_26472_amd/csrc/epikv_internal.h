@@ -423,11 +423,13 @@ constexpr int kLagWgWanted = 512;        // split a plane's rows until this many
 constexpr int kLagPtCache = 1024;        // page-table entries a KV-scorer workgroup keeps in LDS
 // Bytes of a call's rows from which on its first chunks' ranges are found by
 // a launch of their own (split rows only).  It cannot be known here whether
-// a stream is fresh, so later chunks of that size pay for an empty launch:
-// at 64 MiB (1 sequence, 64 planes, 512 rows of 2 KiB) 1-2 us of 25, at 128
-// MiB under 1 us of 37, while the first chunk goes from 88 to 40 us (163 ->
-// 62 us at 128 MiB, 606 -> 190 us at 512 MiB).
-constexpr int64_t kLagFirstBytes = 64 << 20;
+// a stream is fresh, so later chunks of that size pay for an empty launch: at
+// 64 MiB (1 sequence, 64 planes, 512 rows of 2 KiB) 24.0 -> 25.3 us, at 96 MiB
+// 30.2 -> 30.5, at 128 MiB 36.7 -> 37.0 to 37.5, at 512 MiB 101.5 -> 102.5.
+// The first chunk gains 49 us at 64 MiB, which 40 later chunks (20,000 tokens)
+// lose again, and 100 us at 128 MiB (163 -> 63), which takes 125 or more of
+// them (128,000 tokens); 416 us at 512 MiB (606 -> 190).
+constexpr int64_t kLagFirstBytes = 128 << 20;
 constexpr int kLagRowCache = kLagPtCache / 2;  // or row offsets (int64, the same LDS)
 
 // KV-vector scorer shapes (lag: a lag-normalised signal).  Wavefronts per

@@ -1,5 +1,5 @@
 """A Lag-KV stream's first chunk, large enough that its range is found by a
-launch of its own (64 MiB of rows, split between workgroups)."""
+launch of its own (128 MiB of rows, split between workgroups)."""
 import numpy as np
 import pytest
 
@@ -12,14 +12,14 @@ E = K.E
 
 
 @pytest.mark.parametrize("signal,H,d,L,C,B,page,nan", [
-    ("lagkv", 8, 128, 16, 1024, 1, 16, False),      # two row segments, whole shares
-    ("lagkv", 8, 128, 16, 1031, 1, 16, True),       # a NaN key; a short last share
-    ("lagkv", 2, 128, 64, 520, 2, 3, False),        # narrow rows, two shares
-    ("lagkv_key", 16, 128, 17, 1030, 1, 64, False),  # one tensor, four row segments
+    ("lagkv", 8, 128, 32, 1024, 1, 16, False),      # two row segments, whole shares
+    ("lagkv", 8, 128, 32, 1031, 1, 16, True),       # a NaN key; a short last share
+    ("lagkv", 2, 128, 64, 1040, 2, 3, False),        # narrow rows, two shares
+    ("lagkv_key", 16, 128, 33, 1030, 1, 64, False),  # one tensor, four row segments
 ])
 def test_large_first_chunk_matches_oracle(E, signal, H, d, L, C, B, page, nan):
     planes = (2 if signal == "lagkv" else 1) * L
-    assert planes * B * C * H * d * 2 >= 64 << 20
+    assert planes * B * C * H * d * 2 >= 128 << 20
     K._run_kv(E, signal, C, nan=nan, H=H, d=d, L=L, B=B, page=page)
 
 
@@ -29,8 +29,8 @@ def test_fresh_and_carried_sequences_in_one_call(E):
     chunk is one workgroup's."""
     import torch
     g = synth.rng(1812)
-    B, C, L, H, d, page = 2, 1030, 8, 8, 128, 16
-    assert 2 * L * B * C * H * d * 2 >= 64 << 20 > 2 * L * C * H * d * 2
+    B, C, L, H, d, page = 2, 1030, 16, 8, 128, 16
+    assert 2 * L * B * C * H * d * 2 >= 128 << 20 > 2 * L * C * H * d * 2
     Ns = np.array([C, C + 21])
     pt, n_pages = synth.page_tables(Ns, page, g)
     pool = dev(synth.kv_rows(g, (L, 2, n_pages, page, H * d))).view(L, 2, n_pages, page, H, d)
