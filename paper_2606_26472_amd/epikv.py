@@ -191,8 +191,12 @@ def _stream(stream):
     if stream is None:
         import torch
         if torch.cuda.is_initialized():
-            # (the handle alone: building a Stream object costs 1 us)
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            # (the handle alone: building a Stream object costs 1 us; the
+            # names are private, and a torch without them takes that way)
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

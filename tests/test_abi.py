@@ -118,6 +118,25 @@ def test_strerror_covers_every_code(E):
     assert E.strerror(-99) == "unknown status"
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_the_private_names(E, monkeypatch, missing):
+    """The binding reads the current stream's handle through two private
+    names of torch; a torch that lacks one gives it through the public API."""
+    import torch
+
+    class Stream:
+        cuda_stream = 4711
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream())
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: 5, raising=False)
+    assert E._stream(None) == 5
+    monkeypatch.delattr(torch._C, missing)
+    assert E._stream(None) == 4711
+    assert E._stream(9) == 9 and E._stream(Stream()) == 4711
+
+
 # Fake device addresses: aligned, never dereferenced (every call below fails
 # validation on the host).  On a machine with a GPU these calls are skipped:
 # a validation bug there would launch a kernel on addresses that do not
