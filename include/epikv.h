@@ -484,9 +484,9 @@ typedef struct epikv_step_io {
  * and state_out are then not used (may be NULL), and the workspace needs
  * epikv_workspace_bytes(cfg, 0) bytes.
  * The selection runs epikv_select_ws's kernels with their scratch at the
- * start of the workspace, where it is kept from one step to the next (when
- * the chunk lies inside the recency window it runs epikv_select's instead,
- * beside the scoring).
+ * start of the workspace, which any contents may fill (when the chunk lies
+ * inside the recency window it runs epikv_select's instead, beside the
+ * scoring).
  */
 int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
                      hipStream_t stream);
@@ -513,7 +513,7 @@ int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
  * (else EPIKV_EINVAL_PARAM); the address lookup failing returns
  * EPIKV_ELAUNCH.  Every call on one GPU shares its array, which keeps the
  * last call's contents (the step writes everything it reads from it, the
- * selection's scratch through a clearing kernel): calls that overlap in
+ * split selection's scratch included): calls that overlap in
  * time on one GPU -- on two streams, or from two threads -- race and must
  * not be issued.
  */

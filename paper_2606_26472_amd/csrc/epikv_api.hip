@@ -850,9 +850,8 @@ EPIKV_EXPORT int epikv_evict_step(const epikv_cfg* cfg, const epikv_step_io* io,
   if (!io->workspace || io->workspace_bytes < epikv_workspace_bytes(cfg, io->chunk))
     return EPIKV_EWORKSPACE;
   if (!aligned16(io->workspace)) return EPIKV_EALIGN;
-  // Workspace: the selection's scratch first (at a place that does not
-  // depend on the chunk, since it is kept from one call to the next), then
-  // the signal, the Lag-KV partial sums and the compaction's scratch.
+  // Workspace: the split selection's scratch (cleared by each call that uses
+  // it), the signal, the Lag-KV partial sums, the compaction's scratch.
   void* ws_select = io->workspace;
   const size_t sel_bytes = select_scratch_bytes(cfg->batch);
   char* ws = (char*)io->workspace + sel_bytes;

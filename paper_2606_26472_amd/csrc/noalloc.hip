@@ -11,8 +11,8 @@
 // current, and kept in `g_scratch`.  Only that address is ever handed to a
 // kernel.  Every call on one GPU shares the array and it keeps the last
 // call's contents; the step's kernels write every scratch word before they
-// read it (the selection's histograms are cleared by a fill kernel at the
-// start of each call).  Calls that overlap in time on one GPU (two
+// read it (the split selection's scratch is cleared by a launch before it in
+// each call).  Calls that overlap in time on one GPU (two
 // streams, two threads) race on it.
 #include <mutex>
 

@@ -46,10 +46,8 @@ def _expected(pool, pt, keeps, lengths):
 
 CASES = {
     # name: overrides of _run
-    # column slices of 1 KiB and 256 B (the library picks the widest that
-    # still gives 2048 independent walks, with 16- and 32-row tiles), 256 B
-    # with 64-row tiles when there are fewer walks, and 64 B for rows under
-    # 256 B (64- and 256-row tiles)
+    # few planes (rows cut into several slices), more, and enough that rows
+    # stay whole (slices by kind: test_gpu_inplace_tiles.py)
     "narrow_slices": dict(lengths=[300, 90, 500], K=64),
     "mid_slices": dict(lengths=[300, 90, 500, 120, 260, 64, 65, 200], K=64,
                        L=16),
