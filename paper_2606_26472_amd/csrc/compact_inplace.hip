@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kInplaceThreads) void k_inplace_check(InplaceArgs a
 // threads left over).
 // Measured, K + 128 -> K and rows of 2 KiB in 64 planes, a wavefront per walk of
 // 1 KiB or 256-byte slices -> this, in turn on the same buffers: 16 x 4096 rows
-// 3352 -> 3368 us (5.1 TB/s), 1 x 2000 120 -> 106 us, 1 x 300 22.3 -> 18.2 us,
+// 3354 -> 3350 us (5.1 TB/s), 1 x 2000 120 -> 106 us, 1 x 300 22.3 -> 18.2 us,
 // 3 x 700 115.5 -> 111.6 us; rows of 256 bytes (16 x 4096) 441 -> 434 us; of
 // 1536, 768 and 1280 bytes (1 x 2000, 2 x 1000, 4 x 600 rows) 111 -> 82, 57 ->
 // 37 and 95 -> 81 us.  Large batches stay at 5.1 TB/s with either: a plain copy

@@ -533,7 +533,9 @@ int check_compact_inplace(const epikv_cfg* c, const epikv_pool* pool, const int3
 //   fill three rounds;
 // - 512 bytes (2 KiB of wider rows) if they come out at nine tenths of whole
 //   rounds: 8 x 2048 rows of 2 KiB 884 us so, 910 us whole; of 4 KiB 1626 us in
-//   halves, 1700 us whole;
+//   halves, 1700 us whole.  Only below four times as many planes as units: a
+//   workgroup with nothing to move costs 1.4 ns (32 sequences of 2 KiB rows,
+//   none over its budget: check and move 19.4 us so, 10.6 us whole);
 // - the widest that does, or else the one that comes closest: 5 x 2048 rows of
 //   1408 bytes 381 us in eleven slices, 430 us whole.
 void inplace_slices(int64_t planes, int row_vec, int64_t cus, int32_t* n, int32_t* vec) {
@@ -549,7 +551,8 @@ void inplace_slices(int64_t planes, int row_vec, int64_t cus, int32_t* n, int32_
   for (int s = 1; planes * s <= cus && s <= row_vec; ++s)
     if (fits(s) && fill(s) >= 0.6) return take(s);
   const int cols = row_vec > 128 ? 128 : 32;
-  if (planes > cus && row_vec % cols == 0 && fill(row_vec / cols) >= 0.9)
+  if (planes > cus && (row_vec > 128 || planes < 4 * cus) && row_vec % cols == 0 &&
+      fill(row_vec / cols) >= 0.9)
     return take(row_vec / cols);
   double best = -1.0;
   for (int s = 1; s <= row_vec && best < 0.9; ++s)

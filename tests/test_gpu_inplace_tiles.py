@@ -44,7 +44,8 @@ def _slice_cols(planes, row_vec):
         if planes * s <= cus and fill(s) >= 0.6:
             return row_vec // s
     cols = 128 if row_vec > 128 else 32
-    if planes > cus and row_vec % cols == 0 and fill(row_vec // cols) >= 0.9:
+    narrow = planes > cus and (row_vec > 128 or planes < 4 * cus)
+    if narrow and row_vec % cols == 0 and fill(row_vec // cols) >= 0.9:
         return cols
     best = 0
     for s in fits:
